@@ -16,8 +16,7 @@
 // (cin <-> cout): the adjoint of "read x at v + d" is "write to v + d", and
 // the periodic x-y wrap and the zeros beyond the z-ends are their own adjoints
 // under the flip.  The weight gradient sums dZ[v][cout] x[v + d][cin] over all
-// voxels: blocks stage 64 voxels of both in LDS and accumulate on the matrix
-// cores; per-block partial sums are added in a fixed order (deterministic).
+// voxels (fx_unet_wgrad.hip).
 #include "fx_internal.h"
 #include "fx_unet_internal.h"
 #include "../../include/ferrox_unet.h"
@@ -373,104 +372,6 @@ __global__ __launch_bounds__(256) void k_conv3s(const bf16_t *__restrict__ X, in
     }
 }
 
-// Weight gradient of one tap (blockIdx.y): part[bx][tap][cout][cin] =
-// sum over the block's voxels of G[v][cout] X[v + d_tap][cin].  Each round stages
-// 128 voxels of both operands in LDS, transposed ([channel][voxel]) so that every
-// matrix-core fragment is one 8-byte read; staging moves 8 channels (16 bytes) of one
-// voxel per load, its neighbour index worked out once per such piece.
-template <int CIN, int COUT, int XL = CIN>
-__global__ __launch_bounds__(256) void k_wgrad(const bf16_t *__restrict__ X, int ldx, const bf16_t *__restrict__ G,
-                                               int nx, int ny, int nz, float *__restrict__ part) {
-    constexpr int VB = 128;
-    __shared__ bf16_t gt[COUT * VB];
-    __shared__ bf16_t xt[CIN * VB];
-    constexpr int MT = COUT / 16, NC = CIN / 16, T = MT * NC, TPW = (T + 3) / 4;
-    typedef int i4 __attribute__((ext_vector_type(4)));
-    const int tap = blockIdx.y;
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane & 15, kq = lane >> 4;
-    const int n = nx * ny * nz, nchunks = (n + VB - 1) / VB;
-    f4 acc[TPW];
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const int v0 = ch * VB;
-        for (int u = threadIdx.x; u < VB * (COUT / 8); u += 256) {
-            const int vl = u / (COUT / 8), c8 = (u % (COUT / 8)) * 8;
-            const int v = v0 + vl;
-            union {
-                i4 w;
-                bf16_t h[8];
-            } val;
-            val.w = i4{0, 0, 0, 0};
-            if (v < n) val.w = *(const i4 *)(G + (size_t)v * COUT + c8);
-#pragma unroll
-            for (int j2 = 0; j2 < 8; ++j2) gt[(c8 + j2) * VB + vl] = val.h[j2];
-        }
-        for (int u = threadIdx.x; u < VB * (CIN / 8); u += 256) {
-            const int vl = u / (CIN / 8), c8 = (u % (CIN / 8)) * 8;
-            const int v = v0 + vl;
-            union {
-                i4 w;
-                bf16_t h[8];
-            } val;
-            val.w = i4{0, 0, 0, 0};
-            if (v < n) {
-                const int x = v % nx, q = v / nx, y = q % ny, z = q / ny;
-                const int z2 = z + dz;
-                if (z2 >= 0 && z2 < nz) {
-                    int y2 = y + dy, x2 = x + dx;
-                    y2 = y2 < 0 ? y2 + ny : (y2 >= ny ? y2 - ny : y2);
-                    x2 = x2 < 0 ? x2 + nx : (x2 >= nx ? x2 - nx : x2);
-                    if constexpr (XL >= 8) {
-                        val.w = *(const i4 *)(X + (size_t)((z2 * ny + y2) * nx + x2) * ldx + c8);
-                    } else if (c8 == 0) {   // XL = 4 channels present, the rest zero
-                        typedef int i2 __attribute__((ext_vector_type(2)));
-                        const i2 h = *(const i2 *)(X + (size_t)((z2 * ny + y2) * nx + x2) * ldx);
-                        val.w[0] = h[0];
-                        val.w[1] = h[1];
-                    }
-                }
-            }
-#pragma unroll
-            for (int j2 = 0; j2 < 8; ++j2) xt[(c8 + j2) * VB + vl] = val.h[j2];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < VB / 16; ++kk) {
-#pragma unroll
-            for (int q = 0; q < TPW; ++q) {
-                const int tile = wave + 4 * q;
-                if (tile >= T) break;
-                const int mt = tile / NC, nt = tile % NC;
-                const s4 a = *(const s4 *)(gt + (mt * 16 + col) * VB + kk * 16 + 4 * kq);
-                const s4 b = *(const s4 *)(xt + (nt * 16 + col) * VB + kk * 16 + 4 * kq);
-                acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[q], 0, 0, 0);
-            }
-        }
-        __syncthreads();
-    }
-    float *out = part + ((size_t)blockIdx.x * 27 + tap) * COUT * CIN;
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int tile = wave + 4 * q;
-        if (tile >= T) break;
-        const int mt = tile / NC, nt = tile % NC;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[(size_t)(mt * 16 + 4 * kq + r) * CIN + nt * 16 + col] = acc[q][r];
-    }
-}
-
-// dst[i] (+)= sum over p of part[p][i], p in a fixed order.
-__global__ void k_part_sum(const float *__restrict__ part, int nparts, int m, float *__restrict__ dst, int add) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int p = 0; p < nparts; ++p) s += part[(size_t)p * m + i];
-        dst[i] = add ? dst[i] + s : s;
-    }
-}
-
 // ------------------------------------------------------ elementwise parts
 // One thread per (coarse voxel, group of 4 channels): the 8 children of a
 // coarse voxel (low grid nx, ny, nz) are decoded once and moved as 8-byte
@@ -546,23 +447,6 @@ __global__ void k_mask(const float *__restrict__ G, int ldg, const bf16_t *__res
         s4 o;
         for (int j = 0; j < 4; ++j) o[j] = bf2f((bf16_t)y[j]) > 0.f ? (short)f2bf(gv[j]) : (short)0;
         *(s4 *)(Z + v * C + 4 * g) = o;
-    }
-}
-
-// Per-block column sums of a BF16 [n][C] tensor: part[block][c].
-__global__ __launch_bounds__(256) void k_colsum(const bf16_t *__restrict__ Z, int C, size_t n, float *__restrict__ part) {
-    __shared__ float red[256];
-    const int c = threadIdx.x % C, lanes = 256 / C * C;
-    float s = 0.f;
-    if ((int)threadIdx.x < lanes)
-        for (size_t v = blockIdx.x * (size_t)(256 / C) + threadIdx.x / C; v < n; v += (size_t)gridDim.x * (256 / C))
-            s += bf2f(Z[v * C + c]);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    if ((int)threadIdx.x < C) {
-        float t = 0.f;
-        for (int q = threadIdx.x; q < lanes; q += C) t += red[q];
-        part[(size_t)blockIdx.x * C + threadIdx.x] = t;
     }
 }
 
@@ -744,9 +628,7 @@ void conv_launch(const bf16_t *X, int ldx, const bf16_t *W, const float *b, void
                        0, st, X, ldx, W, b, Y, ldy, nx, ny, nz);
 }
 
-// (cin, cout) of the forward layers (weight gradients) and of the convolutions
-// that carry the gradient back through them (input gradients)
-#define FX_WG_PAIRS(F) F(16, 16) F(16, 32) F(32, 32) F(32, 64) F(64, 64) F(96, 32) F(48, 16)
+// (cin, cout) of the convolutions that carry the gradient back through the layers
 #define FX_IG_PAIRS(F) F(16, 16) F(16, 48) F(32, 32) F(32, 96) F(64, 64) F(64, 32) F(32, 16)
 
 // Input-gradient convolutions (out 1: Y = conv, out 2: Y += conv, FP32): NTW = 4 on
@@ -770,22 +652,6 @@ bool conv_any(int cin, int cout, int out, const bf16_t *X, int ldx, const bf16_t
         FX_IG_PAIRS(FX_CONV_CASE)
     }
 #undef FX_CONV_CASE
-    return false;
-}
-
-bool wgrad_any(int cin, int cout, const bf16_t *X, int ldx, const bf16_t *G, int nx, int ny, int nz, float *part,
-               int nparts, hipStream_t st) {
-    if (cin == 16 && cout == 16 && ldx == kInC) {       // the first layer on the 4-channel input
-        hipLaunchKernelGGL((k_wgrad<16, 16, kInC>), dim3(nparts, 27), dim3(256), 0, st, X, ldx, G, nx, ny, nz, part);
-        return true;
-    }
-#define FX_WG_CASE(ci, co)                                                                                        \
-    if (cin == ci && cout == co) {                                                                                \
-        hipLaunchKernelGGL((k_wgrad<ci, co>), dim3(nparts, 27), dim3(256), 0, st, X, ldx, G, nx, ny, nz, part);  \
-        return true;                                                                                              \
-    }
-    FX_WG_PAIRS(FX_WG_CASE)
-#undef FX_WG_CASE
     return false;
 }
 
@@ -904,14 +770,6 @@ fx_status ufail(fx_status s, const char *fmt, ...) {
         if (e_ != hipSuccess) return ufail(FX_EDEVICE, "%s failed: %s", #call, hipGetErrorString(e_)); \
     } while (0)
 
-constexpr int kWgradParts0 = 128;       // weight-gradient partitions on the finest level
-
-int wgrad_parts(size_t n) {
-    const size_t chunks = (n + 63) / 64;
-    const size_t p = chunks / 32;       // at least 32 chunks per block
-    return (int)(p < 1 ? 1 : (p > kWgradParts0 ? kWgradParts0 : p));
-}
-
 struct Carve {
     char *base;
     size_t off = 0;
@@ -978,10 +836,9 @@ size_t carve_unet(fx_unet *u, void *ws) {
         size_t pf = 0;
         for (int i = 0; i < NLAYER; ++i) {
             const Layer &L = lay.L[i];
-            const size_t n = L.level == 0 ? n0 : (L.level == 1 ? n1 : n2);
-            pf = std::max(pf, (size_t)wgrad_parts(n) * 27 * L.cin * L.cout);
+            pf = std::max(pf, wgrad_part_floats(L.cin, L.cout, u->nx >> L.level, u->ny >> L.level, u->nz >> L.level));
         }
-        pf = std::max(pf, (size_t)8192 * 64);           // column-sum partials
+        pf = std::max(pf, (size_t)256 * 17);            // the head's partial sums
         u->part_floats = pf;
         u->part = cv.take<float>(pf);
     } else {
@@ -1066,25 +923,13 @@ void enqueue_forward(fx_unet *u) {
     }
 }
 
-// Bias gradient of layer l from its BF16 output gradient Z ([n][cout]).
-void bias_grad(fx_unet *u, int l, const bf16_t *Z, size_t n) {
-    const Layer &L = layout().L[l];
-    const int nb = (int)std::min<size_t>(128, (n + 255) / 256);
-    hipLaunchKernelGGL(k_colsum, dim3(nb), dim3(256), 0, u->st, Z, L.cout, n, u->part);
-    hipLaunchKernelGGL(k_part_sum, dim3(1), dim3(64), 0, u->st, u->part, nb, L.cout, u->grad + L.boff, 0);
-}
-
 // Weight and bias gradient of layer l (input X, ld ldx; output gradient Z),
 // and optionally its input gradient into G (FP32, ld ldg; add = accumulate).
 void layer_backward(fx_unet *u, int l, const bf16_t *X, int ldx, const bf16_t *Z, float *G, int ldg, int add) {
     const Layer &L = layout().L[l];
     const Dims d = dims_of(u, L.level);
-    const size_t n = (size_t)d.nx * d.ny * d.nz;
-    const int np = wgrad_parts(n);
-    wgrad_any(L.cin, L.cout, X, ldx, Z, d.nx, d.ny, d.nz, u->part, np, u->st);
-    const int m = 27 * L.cin * L.cout;
-    hipLaunchKernelGGL(k_part_sum, grid_for(m), dim3(256), 0, u->st, u->part, np, m, u->grad + L.woff, 0);
-    bias_grad(u, l, Z, n);
+    // the bias follows the weights in the parameter vector
+    wgrad(L.cin, L.cout, ldx == kInC ? kInC : 16, X, ldx, Z, d.nx, d.ny, d.nz, u->part, u->grad + L.woff, u->st);
     if (G)
         conv_any(L.cout, L.cin, add ? 2 : 1, Z, L.cout, wf_of(u, l), nullptr, G, ldg, d.nx, d.ny, d.nz, u->staged, u->st);
 }
@@ -1105,7 +950,7 @@ void enqueue_backward(fx_unet *u, const float *tg) {
     // head
     hipLaunchKernelGGL(k_head_bwd, dim3(nbl), dim3(256), 0, st, u->dout, u->a_d0b, u->theta + lay.head_off, u->z0,
                        u->part, n0);
-    hipLaunchKernelGGL(k_part_sum, dim3(1), dim3(64), 0, st, u->part, nbl, 17, u->grad + lay.head_off, 0);
+    part_sum(u->part, nbl, 17, u->grad + lay.head_off, st);
     // level 0, up
     layer_backward(u, D0B, u->a_d0a, 16, u->z0, u->g0_16, 16, 0);
     mask(u, u->g0_16, 16, u->a_d0a, 16, u->z0, 16, n0);
