@@ -1850,15 +1850,15 @@ __global__ __launch_bounds__(TbShape<TbCfg<T>::post_q>::threads) void k_post_tb(
 }
 
 // --------------------------------------------- coarse levels in one workgroup
-// Quotient q / d for 0 <= q < 2^31 and 1 <= d < 2^16 without an integer division:
-// (q + 1/2) / d lies at least 1/(2d) >= 2^-17 from the next integer, while the
-// product with the rounded reciprocal is off by at most 2^-52 q/d < 2^-21.
+// Quotient q / d for 0 <= q < 2^20 and 1 <= d without an integer division: (q + 1/2) / d
+// lies at least 1/(2d) from the next integer, while the rounded product is off by at most
+// 2^-22 q/d (every level of the coarse kernel has fewer than 2^14 cells).
 struct FDiv {
     int d;
-    double inv;
+    float inv;
 };
-__device__ __forceinline__ FDiv fdiv_of(int d) { return {d, 1.0 / (double)d}; }
-__device__ __forceinline__ int fquo(int q, const FDiv &f) { return (int)(((double)q + 0.5) * f.inv); }
+__device__ __forceinline__ FDiv fdiv_of(int d) { return {d, 1.0f / (float)d}; }
+__device__ __forceinline__ int fquo(int q, const FDiv &f) { return (int)(((float)q + 0.5f) * f.inv); }
 
 // (i, j, k) of natural index c on an nx x ny x nz level
 struct Split3 {
@@ -1871,93 +1871,240 @@ __device__ __forceinline__ void split_c(int c, const Split3 &s, int &i, int &j, 
     j = row - k * s.fy.d;
 }
 
-// A coarse-kernel phase: the whole workgroup strides over the level's cells,
-// and a workgroup barrier separates it from the next phase.
-template <typename V>
-__device__ void smooth_color(const V &L, int color, int zero_init) {
-    using T = typename V::value_type;
-    const int st = (int)blockDim.x;
-    if (L.rb) {
-        // gs_cell on split storage with the indices written out: the cell's pair q, its
-        // x neighbours at the pairs of i +- 1 in its row, the others at pair q of the
-        // neighbouring row or plane (the other colour's array throughout); the sum in
-        // nb_sum's order, the divisor as diag_of forms it
-        const int hx = L.nx >> 1;
-        const int plane = hx * L.ny;
-        const int n = plane * L.nz;
+constexpr int kCoarseThreads = 1024;
+
+// A coarse-kernel phase: the whole workgroup works on the level's cells, and a workgroup
+// barrier separates it from the next phase.  A phase is latency: one chain of LDS reads,
+// FP64 arithmetic and a store, so what a thread needs of its cells for all sweeps of a level
+// (right-hand sides, reciprocal diagonals, coefficients, neighbour offsets) is worked out
+// once and held in registers.
+//
+// Red/black level: NP storage pairs (a red and a black cell of one row) per thread.  The
+// pair's red and black cells are each other's x neighbours; their other x neighbour lies in
+// the pair dx away, the y and z neighbours in pairs oy, oz away (all in the other colour's
+// array).  Absent neighbours (z-ends, ny = 1) weigh 0 and point at the pair itself.
+template <typename T, int NP>
+struct RbCells {
+    T r[2][NP], iv[2][NP], cx[NP], cy[NP], cm[NP], cp[NP];
+    int q[NP], dx[2][NP], oy[2][NP], oz[2][NP];
+    bool on[NP];
+
+    __device__ __forceinline__ void load(const Lv<T, 3> &L) {
+        const int hx = L.nx >> 1, plane = hx * L.ny, n = plane * L.nz;
         const int hsz = plane * (L.sig_hi - L.sig_lo);
-        T FX_AS(3) *es = L.e + (color ? n : 0);
-        const T FX_AS(3) *eo = L.e + (color ? 0 : n);
-        const T FX_AS(3) *rs = L.r + (color ? n : 0);
-        const T FX_AS(3) *ss = L.sig + (color ? hsz : 0);
         const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
-        for (int q = threadIdx.x; q < n; q += st) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int c = threadIdx.x + p * kCoarseThreads;
+            on[p] = c < n;
+            q[p] = on[p] ? c : 0;
             int m, j, k;
-            split_c(q, sp, m, j, k);
-            T d = L.dg[k];
-            if (k >= L.sig_lo && k < L.sig_hi) d += ss[q - L.sig_lo * plane];
-            if (zero_init) {
-                es[q] = rs[q] / d;
-                continue;
+            split_c(q[p], sp, m, j, k);
+            const int par = (j + k) & 1;               // the red cell is at 2m + par
+            const int up = m + 1 == hx ? 1 - hx : 1, dn = m == 0 ? hx - 1 : -1;
+            dx[0][p] = par ? up : dn;
+            dx[1][p] = par ? dn : up;
+            oy[0][p] = L.ny > 1 ? (wrap_p(j, L.ny) - j) * hx : 0;
+            oy[1][p] = L.ny > 1 ? (wrap_m(j, L.ny) - j) * hx : 0;
+            oz[0][p] = k > 0 ? -plane : 0;
+            oz[1][p] = k < L.nz - 1 ? plane : 0;
+            cx[p] = L.cxy[k];
+            cy[p] = L.ny > 1 ? cx[p] : T(0);
+            cm[p] = k > 0 ? L.czm[k] : T(0);
+            cp[p] = k < L.nz - 1 ? L.czp[k] : T(0);
+            const bool hs = k >= L.sig_lo && k < L.sig_hi;
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2) {
+                r[c2][p] = L.r[c2 * n + q[p]];
+                T d = L.dg[k];
+                if (hs) d += L.sig[c2 * hsz + q[p] - L.sig_lo * plane];
+                iv[c2][p] = T(1) / d;
             }
-            const int i = 2 * m + ((color + j + k) & 1);
-            const int row = q - m;
-            const int ip = i + 1 == L.nx ? 0 : i + 1, im = i == 0 ? L.nx - 1 : i - 1;
-            T s = 0;
-            const T cx = L.cxy[k];
-            s += cx * (eo[row + (ip >> 1)] + eo[row + (im >> 1)]);
-            if (L.ny > 1) s += cx * (eo[q + (wrap_p(j, L.ny) - j) * hx] + eo[q + (wrap_m(j, L.ny) - j) * hx]);
-            if (k > 0) s += L.czm[k] * eo[q - plane];
-            if (k < L.nz - 1) s += L.czp[k] * eo[q + plane];
-            es[q] = (rs[q] + s) / d;
-        }
-    } else {
-        const int n = L.nx * L.ny * L.nz;
-        const Split3 sp{fdiv_of(L.nx), fdiv_of(L.ny)};
-        for (int c = threadIdx.x; c < n; c += st) {
-            int i, j, k;
-            split_c(c, sp, i, j, k);
-            if (nat_color(L, i, j, k) == color) gs_cell(L, i, j, k, zero_init);
-            else if (zero_init) L.e[cidx(L, i, j, k)] = T(0);
         }
     }
-}
-
-// One full Gauss-Seidel sweep (2 colours on split levels, 4 otherwise).
-template <typename V>
-__device__ void smooth_sweep(const V &L, int zero_init) {
-    const int ncol = L.rb ? 2 : 4;
-    for (int c = 0; c < ncol; ++c) {
-        smooth_color(L, c, zero_init && c == 0);
+    // neighbour sum of colour c2's cell of pair p
+    __device__ __forceinline__ T nb(const T FX_AS(3) *eo, int c2, int p) const {
+        const T FX_AS(3) *e = eo + q[p];
+        const T x = e[0] + e[dx[c2][p]], y = e[oy[0][p]] + e[oy[1][p]];
+        return fmad(cp[p], e[oz[1][p]], fmad(cm[p], e[oz[0][p]], fmad(cy[p], y, cx[p] * x)));
+    }
+    __device__ __forceinline__ void half_sweep(const Lv<T, 3> &L, int c2, int zero_init) const {
+        const int n = (L.nx >> 1) * L.ny * L.nz;
+        T FX_AS(3) *es = L.e + c2 * n;
+        const T FX_AS(3) *eo = L.e + (1 - c2) * n;
+        T v[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) v[p] = (zero_init ? r[c2][p] : r[c2][p] + nb(eo, c2, p)) * iv[c2][p];
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (on[p]) es[q[p]] = v[p];
         __syncthreads();
     }
+    // the red cells' residual into their own e (dead until the next red half-sweep)
+    __device__ __forceinline__ void red_residual(const Lv<T, 3> &L) const {
+        const int hx = L.nx >> 1, plane = hx * L.ny, n = plane * L.nz;
+        const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
+        T v[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int k = fquo(fquo(q[p], sp.fx), sp.fy);
+            T d = L.dg[k];
+            if (k >= L.sig_lo && k < L.sig_hi) d += L.sig[q[p] - L.sig_lo * plane];
+            v[p] = r[0][p] - fmad(d, L.e[q[p]], -nb(L.e + n, 0, p));
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            if (on[p]) L.e[q[p]] = v[p];
+        __syncthreads();
+    }
+};
+
+// Restriction of a red/black level halved in x and y from the red residuals just formed: the
+// red child of row (j, k) of coarse column I is the red cell of pair I of that row.
+template <typename T, typename X_>
+__device__ __forceinline__ void restrict_pairs(const Lv<T, 3> &F, const Lv<T, 3> &C, const X_ &X) {
+    const int hx = F.nx >> 1, n = C.nx * C.ny * C.nz;
+    const Split3 sp{fdiv_of(C.nx), fdiv_of(C.ny)};
+    for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
+        int I, J, K;
+        split_c(c, sp, I, J, K);
+        const int ks = X.cks[K], cnt = X.ccnt[K];
+        double sr = 0.0, ss = 0.0;
+        for (int dz = 0; dz < cnt; ++dz) {
+            const int k = ks + dz;
+            const double wz = (double)X.fthick[k] / (double)X.cthick[K];
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy) {
+                const int j = 2 * J + dy;
+                sr += wz * (double)F.e[(k * F.ny + j) * hx + I];
+                if (has_sig(F, k)) {
+#pragma unroll
+                    for (int dx = 0; dx < 2; ++dx) ss += wz * (double)F.sig[sidx(F, 2 * I + dx, j, k)];
+                }
+            }
+        }
+        C.r[cidx(C, I, J, K)] = (T)(sr * 0.25);
+        if (has_sig(C, K)) C.sig[sidx(C, I, J, K)] = (T)(ss * 0.25);
+    }
+    __syncthreads();
 }
 
-// Restriction into level C and prolongation from it, as one phase each.
-// On a red/black level halved in x and y both take the global kernels' forms (every load
-// of a coarse cell's children before its arithmetic; black cells alone corrected), which
-// compute what restrict_cell and prolong_cell compute, in the same order.
+template <typename T, int NP, typename X_>
+__device__ __forceinline__ void co_pre_rb(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
+    RbCells<T, NP> c;
+    c.load(L);
+    for (int s = 0; s < nu; ++s) {
+        c.half_sweep(L, 0, s == 0);
+        c.half_sweep(L, 1, 0);
+    }
+    if (X.xy == 1) {
+        c.red_residual(L);
+        restrict_pairs(L, C, X);
+    }
+}
+template <typename T, int NP>
+__device__ __forceinline__ void co_post_rb(const Lv<T, 3> &L, int nu) {
+    RbCells<T, NP> c;
+    c.load(L);
+    for (int s = 0; s < nu; ++s) {
+        c.half_sweep(L, 0, 0);
+        c.half_sweep(L, 1, 0);
+    }
+}
+
+// Plainly stored level: NP cells per thread, each of one of the four colours.
+template <typename T, int NP>
+struct NatCells {
+    T r[NP], iv[NP], cx[NP], cm[NP], cp[NP];
+    int c[NP], ox[2][NP], oy[2][NP], oz[2][NP], col[NP];   // col -1: no cell
+
+    __device__ __forceinline__ void load(const Lv<T, 3> &L) {
+        const int plane = L.nx * L.ny, n = plane * L.nz;
+        const Split3 sp{fdiv_of(L.nx), fdiv_of(L.ny)};
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int cc = threadIdx.x + p * kCoarseThreads;
+            const bool on = cc < n;
+            c[p] = on ? cc : 0;
+            int i, j, k;
+            split_c(c[p], sp, i, j, k);
+            ox[0][p] = wrap_p(i, L.nx) - i;
+            ox[1][p] = wrap_m(i, L.nx) - i;
+            oy[0][p] = (wrap_p(j, L.ny) - j) * L.nx;
+            oy[1][p] = (wrap_m(j, L.ny) - j) * L.nx;
+            oz[0][p] = k > 0 ? -plane : 0;
+            oz[1][p] = k < L.nz - 1 ? plane : 0;
+            col[p] = on ? nat_color(L, i, j, k) : -1;
+            cx[p] = L.cxy[k];
+            cm[p] = k > 0 ? L.czm[k] : T(0);
+            cp[p] = k < L.nz - 1 ? L.czp[k] : T(0);
+            r[p] = L.r[c[p]];
+            iv[p] = T(1) / diag_of(L, i, j, k);
+        }
+    }
+    __device__ __forceinline__ void sweep(const Lv<T, 3> &L, int zero_init) const {
+        const T wx = L.nx > 1 ? T(1) : T(0), wy = L.ny > 1 ? T(1) : T(0);
+        for (int color = 0; color < 4; ++color) {
+            const int zi = zero_init && color == 0;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                if (col[p] == color) {
+                    T s = 0;
+                    if (!zi) {
+                        const T FX_AS(3) *e = L.e + c[p];
+                        const T x = wx * (e[ox[0][p]] + e[ox[1][p]]), y = wy * (e[oy[0][p]] + e[oy[1][p]]);
+                        s = fmad(cp[p], e[oz[1][p]], fmad(cm[p], e[oz[0][p]], fmad(cx[p], y, cx[p] * x)));
+                    }
+                    L.e[c[p]] = (r[p] + s) * iv[p];
+                } else if (zi && col[p] >= 0) {
+                    L.e[c[p]] = T(0);
+                }
+            }
+            __syncthreads();
+        }
+    }
+};
+template <typename T, int NP>
+__device__ __forceinline__ void co_smooth_nat(const Lv<T, 3> &L, int nu, int zero_init) {
+    NatCells<T, NP> c;
+    c.load(L);
+    for (int s = 0; s < nu; ++s) c.sweep(L, zero_init && s == 0);
+}
+
+// Pre-smoothing and restriction, and prolongation and post-smoothing, of one level.  A level
+// here holds e and r in kCoarseLdsBytes, so at most 4096 cells in FP64 and 8192 in FP32.
+static_assert(kCoarseLdsBytes / (2 * sizeof(float)) <= 8 * kCoarseThreads, "cells per thread");
 template <typename T, typename X_>
-__device__ void restrict_phase(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X) {
+__device__ __forceinline__ void co_down(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
+    if (L.rb) {
+        const int n = (L.nx >> 1) * L.ny * L.nz;
+        if (n <= kCoarseThreads) co_pre_rb<T, 1>(L, C, X, nu);
+        else if (n <= 2 * kCoarseThreads) co_pre_rb<T, 2>(L, C, X, nu);
+        else if constexpr (sizeof(T) == 4) co_pre_rb<T, 4>(L, C, X, nu);
+        if (X.xy == 1) return;
+    } else {
+        const int n = L.nx * L.ny * L.nz;
+        if (n <= kCoarseThreads) co_smooth_nat<T, 1>(L, nu, 1);
+        else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4>(L, nu, 1);
+        else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8>(L, nu, 1);
+    }
     const int n = C.nx * C.ny * C.nz;
     const Split3 sp{fdiv_of(C.nx), fdiv_of(C.ny)};
-    const bool rbxy = L.rb && X.xy == 1;
-    for (int c = threadIdx.x; c < n; c += blockDim.x) {
+    for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
         int I0, J0, K0;
         split_c(c, sp, I0, J0, K0);
-        if (rbxy) restrict_cell_rbxy(L, C, X, I0, J0, K0);
-        else restrict_cell(L, C, X, I0, J0, K0);
+        restrict_cell(L, C, X, I0, J0, K0);
     }
     __syncthreads();
 }
 template <typename T, typename X_>
-__device__ void prolong_phase(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X) {
+__device__ __forceinline__ void co_up(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
     if (L.rb) {
         const int hx = L.nx >> 1;
         const int n = hx * L.ny * L.nz;
         T FX_AS(3) *eb = L.e + n;
         const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
-        for (int q = threadIdx.x; q < n; q += blockDim.x) {
+        for (int q = threadIdx.x; q < n; q += kCoarseThreads) {
             int m, j, k;
             split_c(q, sp, m, j, k);
             const int i = 2 * m + ((1 + j + k) & 1);
@@ -1965,32 +2112,56 @@ __device__ void prolong_phase(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X)
                         : X.xy == 2 ? prolong_value<2>(C, X, i, j, k) : prolong_value<0>(C, X, i, j, k);
             eb[q] += v;
         }
+        __syncthreads();
+        if (n <= kCoarseThreads) co_post_rb<T, 1>(L, nu);
+        else if (n <= 2 * kCoarseThreads) co_post_rb<T, 2>(L, nu);
+        else if constexpr (sizeof(T) == 4) co_post_rb<T, 4>(L, nu);
     } else {
         const int n = L.nx * L.ny * L.nz;
         const Split3 sp{fdiv_of(L.nx), fdiv_of(L.ny)};
-        for (int c = threadIdx.x; c < n; c += blockDim.x) {
+        for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
             int i, j, k;
             split_c(c, sp, i, j, k);
             prolong_cell(L, C, X, i, j, k);
         }
+        __syncthreads();
+        if (n <= kCoarseThreads) co_smooth_nat<T, 1>(L, nu, 0);
+        else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4>(L, nu, 0);
+        else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8>(L, nu, 0);
     }
-    __syncthreads();
 }
 
-// Dot product over a whole workgroup, accumulated in double in a fixed order
-// (deterministic); every thread returns the total.
-template <typename P>
-__device__ double block_dot(P x, P y, int n, double FX_AS(3) *red) {
-    const int tid = threadIdx.x;
-    double s = 0.0;
-    for (int c = tid; c < n; c += blockDim.x) s += (double)x[c] * (double)y[c];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = s;
+// Sum over the 64 lanes of a wave in a fixed order with DPP adds (row shifts, then the two
+// row broadcasts leave the total in lane 63); every lane gets the same bits.  Six shuffles
+// through the LDS unit took several times as long.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+    v = dpp_add<0x111, 0xf>(v);                        // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);                        // row_bcast 15, 31
+    v = dpp_add<0x143, 0xc>(v);
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Sum over the workgroup in a fixed order; every thread gets the total.  red holds one
+// partial per wave; the caller's next write to it comes after another barrier.
+__device__ __forceinline__ double block_total(double v, double FX_AS(3) *red) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double t = 0.0;
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) t += red[q];
-    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kCoarseThreads / 64; ++q) t += red[q];
     return t;
 }
 
@@ -2000,14 +2171,6 @@ __device__ double block_dot(P x, P y, int n, double FX_AS(3) *red) {
 // residual.  Unlike a fixed number of Gauss-Seidel sweeps this also solves
 // coarsest levels that keep many cells in x and y (odd lateral sizes stop the
 // x-y coarsening early).
-// Sum over the 64 lanes of a wave, formed in lane 0 in a fixed order and
-// broadcast (every lane gets the same bits).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    return __shfl(v, 0, 64);
-}
-
 // The same conjugate gradients for a bottom level of at most 64 cells, run by
 // the first wave alone with one cell per lane: the operator's neighbours are
 // read from other lanes' registers, the dot products are wave sums, and no
@@ -2063,50 +2226,93 @@ __device__ void bottom_cg_wave(const Lv<T, 3> &B, int iters, double tol2) {
     }
 }
 
+// A thread per cell, NP cells each: x, r, the search direction's own value and the operator's
+// row stay in registers, the direction is shared through LDS (ps).  red, red2: two sets of partials,
+// so that a sum's partials are not overwritten while another wave still reads them.
+template <typename T, int NP>
+__device__ __forceinline__ void bottom_cg_block(const Lv<T, 3> &B, T FX_AS(3) *ps, double FX_AS(3) *red,
+                                                double FX_AS(3) *red2, int iters, double tol2) {
+    const int n = B.nx * B.ny * B.nz, plane = B.nx * B.ny;
+    const Split3 sp{fdiv_of(B.nx), fdiv_of(B.ny)};
+    double r[NP], x[NP], d[NP], p[NP], cx[NP], cy[NP], cm[NP], cp[NP];
+    int c[NP], ci[NP], ox[2][NP], oy[2][NP], oz[2][NP];
+    bool on[NP];
+    double rr = 0.0;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        const int cc = threadIdx.x + u * kCoarseThreads;
+        on[u] = cc < n;
+        c[u] = on[u] ? cc : 0;
+        int i, j, k;
+        split_c(c[u], sp, i, j, k);
+        ci[u] = cidx(B, i, j, k);
+        ox[0][u] = wrap_p(i, B.nx) - i;
+        ox[1][u] = wrap_m(i, B.nx) - i;
+        oy[0][u] = (wrap_p(j, B.ny) - j) * B.nx;
+        oy[1][u] = (wrap_m(j, B.ny) - j) * B.nx;
+        oz[0][u] = k > 0 ? -plane : 0;
+        oz[1][u] = k < B.nz - 1 ? plane : 0;
+        cx[u] = on[u] && B.nx > 1 ? (double)B.cxy[k] : 0.0;
+        cy[u] = on[u] && B.ny > 1 ? (double)B.cxy[k] : 0.0;
+        cm[u] = on[u] && k > 0 ? (double)B.czm[k] : 0.0;
+        cp[u] = on[u] && k < B.nz - 1 ? (double)B.czp[k] : 0.0;
+        d[u] = on[u] ? (double)diag_of(B, i, j, k) : 0.0;
+        r[u] = on[u] ? (double)B.r[ci[u]] : 0.0;
+        x[u] = 0.0;
+        p[u] = r[u];
+        rr += r[u] * r[u];
+        if (on[u]) ps[c[u]] = (T)p[u];
+    }
+    rr = block_total(rr, red);                         // its barrier also publishes ps
+    const double stop = tol2 * rr;
+    for (int it = 0; it < iters && rr > stop; ++it) {
+        double q[NP], pq = 0.0;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const T FX_AS(3) *e = ps + c[u];
+            p[u] = on[u] ? (double)e[0] : 0.0;         // the direction as its neighbours see it
+            q[u] = d[u] * p[u] - cx[u] * ((double)e[ox[0][u]] + (double)e[ox[1][u]]) -
+                   cy[u] * ((double)e[oy[0][u]] + (double)e[oy[1][u]]) - cm[u] * (double)e[oz[0][u]] -
+                   cp[u] * (double)e[oz[1][u]];
+            pq += p[u] * q[u];
+        }
+        pq = block_total(pq, red2);
+        if (!(pq > 0.0)) break;
+        const double alpha = rr / pq;
+        double rn = 0.0;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            x[u] += alpha * p[u];
+            r[u] -= alpha * q[u];
+            rn += r[u] * r[u];
+        }
+        rn = block_total(rn, red);
+        const double beta = rn / rr;
+        rr = rn;
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (on[u]) ps[c[u]] = (T)(r[u] + beta * p[u]);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u)
+        if (on[u]) B.e[ci[u]] = (T)x[u];
+    __syncthreads();
+}
+
 template <typename T>
-__device__ void bottom_cg(const Lv<T, 3> &B, T FX_AS(3) *p, T FX_AS(3) *q, double FX_AS(3) *red, int iters,
-                          double tol2) {
+__device__ __forceinline__ void bottom_cg(const Lv<T, 3> &B, T FX_AS(3) *p, double FX_AS(3) *red, double FX_AS(3) *red2,
+                                          int iters, double tol2) {
     const int n = B.nx * B.ny * B.nz;
     if (n <= 64) {
         if (threadIdx.x < 64) bottom_cg_wave(B, iters, tol2);
         __syncthreads();
-        return;
-    }
-    T FX_AS(3) *e = B.e;
-    T FX_AS(3) *r = B.r;
-    const Split3 sp{fdiv_of(B.nx), fdiv_of(B.ny)};
-    for (int c = threadIdx.x; c < n; c += blockDim.x) {
-        e[c] = T(0);
-        p[c] = r[c];
-    }
-    __syncthreads();
-    double rr = block_dot(r, r, n, red);
-    const double stop = tol2 * rr;
-    for (int it = 0; it < iters && rr > stop; ++it) {
-        for (int c = threadIdx.x; c < n; c += blockDim.x) {
-            int i, j, k;
-            split_c(c, sp, i, j, k);
-            const int ci = cidx(B, i, j, k);
-            q[ci] = diag_of(B, i, j, k) * p[ci] - nb_sum(B, p, i, j, k);
-        }
-        __syncthreads();
-        const double pq = block_dot(p, q, n, red);
-        if (!(pq > 0.0)) break;
-        const double alpha = rr / pq;
-        for (int c = threadIdx.x; c < n; c += blockDim.x) {
-            e[c] += (T)(alpha * (double)p[c]);
-            r[c] -= (T)(alpha * (double)q[c]);
-        }
-        __syncthreads();
-        const double rn = block_dot(r, r, n, red);
-        const double beta = rn / rr;
-        rr = rn;
-        for (int c = threadIdx.x; c < n; c += blockDim.x) p[c] = r[c] + (T)(beta * (double)p[c]);
-        __syncthreads();
+    } else if (n <= kCoarseThreads) {
+        bottom_cg_block<T, 1>(B, p, red, red2, iters, tol2);
+    } else {
+        bottom_cg_block<T, 2>(B, p, red, red2, iters, tol2);
     }
 }
-
-constexpr int kCoarseThreads = 1024;
 
 // A block per instance: the V-cycle from level lc down to the coarsest with
 // every level's e, r, sigma and coefficient tables resident in LDS.
@@ -2246,18 +2452,10 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(const Inst<T> *I, Ins
     __syncthreads();
     const int light = sta->light;
     const int nu1 = light ? 1 : A.nu1, nu2 = light ? 1 : A.nu2;
-    for (int q = 0; q < nl - 1; ++q) {
-        const Lv<T, 3> L = lvl(q);
-        for (int s = 0; s < nu1; ++s) smooth_sweep(L, s == 0);
-        restrict_phase(L, lvl(q + 1), xlds(q));
-    }
-    bottom_cg<T>(lvl(nl - 1), (T FX_AS(3) *)(lds + A.off_p), (T FX_AS(3) *)(lds + A.off_q),
-                 (double FX_AS(3) *)(lds + A.off_red), A.bottom_iters, A.bottom_tol2);
-    for (int q = nl - 2; q >= 0; --q) {
-        const Lv<T, 3> L = lvl(q);
-        prolong_phase(L, lvl(q + 1), xlds(q));
-        for (int s = 0; s < nu2; ++s) smooth_sweep(L, 0);
-    }
+    for (int q = 0; q < nl - 1; ++q) co_down(lvl(q), lvl(q + 1), xlds(q), nu1);
+    bottom_cg<T>(lvl(nl - 1), (T FX_AS(3) *)(lds + A.off_p), (double FX_AS(3) *)(lds + A.off_red),
+                 (double FX_AS(3) *)(lds + A.off_q), A.bottom_iters, A.bottom_tol2);
+    for (int q = nl - 2; q >= 0; --q) co_up(lvl(q), lvl(q + 1), xlds(q), nu2);
     {
         const Lv<T, 1> G = gview(A.lv[l0]);
         const Lv<T, 3> L0 = lvl(0);
