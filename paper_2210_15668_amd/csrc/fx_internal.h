@@ -101,6 +101,7 @@ struct InstState {
     int parked;                       // run target reached or a solve failed
     int solves, failed, total_cycles, max_cycles_step;
     double v_top;                     // gate potential of the current solve
+    double v_done;                    // gate potential of the last finalized solve
     double dt;                        // time step of the run
     double rn2, fn2;                  // ||r||^2, ||f||^2 of the latest residual (scaled units)
 };
@@ -186,19 +187,16 @@ struct Work {
 };
 
 // ------------------------------------------------------------------ launchers
-// sel = 1 restricts a launch to the instances starting a time step in the
-// current advance slot; sel = 0 covers every instance.
-template <typename T> void launch_tdgl(const Inst<T> *I, const Work &w, int sel, hipStream_t st);
-// corrector of a second-order step, for the instances flagged in this advance slot:
-// P^n := (P^n + P*)/2 + dt/2 f(P*, phi*), in the buffer that holds P^n
-template <typename T> void launch_tdgl_corr(const Inst<T> *I, const Work &w, hipStream_t st);
+template <typename T> void launch_tdgl(const Inst<T> *I, const Work &w, hipStream_t st);
+// the field work of an advance slot: TDGL update (or corrector), starting iterates and, with
+// rec, the face sums of completed steps (launch_reduce's mode 0 writes the records)
+template <typename T> void launch_fields(const Inst<T> *I, const Work &wt, const Work &we, int rec, hipStream_t st);
 template <typename T> void launch_flip(const Inst<T> *I, int ninst, hipStream_t st);
-// Interface charge Q and average ferroelectric voltage V_fe.  record 0: every instance's
-// current state into out[2 i], out[2 i + 1] (NaN without an interface); record 1: the
-// instances that completed a time step in this advance slot, into their per-step record.
-template <typename T> void launch_qv(const Inst<T> *I, int ninst, int record, double *out, hipStream_t st);
+// Interface charge Q and average ferroelectric voltage V_fe of every instance's current state
+// into out[2 i], out[2 i + 1] (NaN without an interface).
+template <typename T> void launch_qv(const Inst<T> *I, int ninst, double *out, hipStream_t st);
+// sel = 1: the instances starting a time step in the current advance slot; 0: every instance
 template <typename T> void launch_begin(const Inst<T> *I, InstState *S, int ninst, int sel, hipStream_t st);
-template <typename T> void launch_extrap(const Inst<T> *I, const Work &w, hipStream_t st);
 // Work tables of the residual: cell0 -- every instance (mode 0, the current
 // iterate; after a cycle the kernel skips the instances of cell2); cell2 --
 // instances whose update is not folded into the smoother (mode 2: forms
@@ -211,7 +209,9 @@ struct ResWork {
 // where the update is not folded into the smoother).
 // any_fd: some instance takes Fermi-Dirac carriers (else the kernel without that branch)
 template <typename T> void launch_residual(const Inst<T> *I, const ResWork &w, int after_cycle, int any_fd, hipStream_t st);
-template <typename T> void launch_reduce(const Inst<T> *I, InstState *S, int ninst, int count_cycle, hipStream_t st);
+// mode 0: a solve's starting residual (rec: and the Q-V records); 1: after a cycle; 2: after a
+// cycle of a run, finalizing stopped solves and starting the next ones
+template <typename T> void launch_reduce(const Inst<T> *I, InstState *S, int ninst, int mode, int rec, hipStream_t st);
 // Launch shape of one level's smoother: tile of 2^lbx x 2^(8-lbx) threads,
 // zt planes per thread, w8: register budget for 8 waves per SIMD.  Only the
 // division of the work changes, never a cell's arithmetic.

@@ -76,8 +76,7 @@ struct Blk {
     bool ok;
 };
 
-__device__ __forceinline__ Blk find_block(const Work &w) {
-    const int nb = gridDim.x, b = blockIdx.x;
+__device__ __forceinline__ Blk find_block(const Work &w, int b, int nb) {
     const int g = (b & 7) * (nb >> 3) + (b >> 3);
     Blk r;
     r.ok = g < w.total;
@@ -99,6 +98,7 @@ __device__ __forceinline__ Blk find_block(const Work &w) {
     r.t = g - pre[r.inst];
     return r;
 }
+__device__ __forceinline__ Blk find_block(const Work &w) { return find_block(w, blockIdx.x, gridDim.x); }
 
 struct T3 {
     int tx, ty, tz;
@@ -453,46 +453,32 @@ __device__ __forceinline__ double tdgl_force(const Inst<T> &a, const double FX_A
     return landau - a.g44 * (dxx + dyy) - a.g11 * dzz + dphi;
 }
 
+// The update of one tile: P^{n+1} into dst.  Euler (Step 1a): src + dt f(src, phi^n).
+// Corrector (Step 2a): P^{n+1} = P^n + dt/2 f(P^n, phi^n) + dt/2 f(P*, phi*); with
+// P* = P^n + dt f(P^n, phi^n) this is (P^n + P*)/2 + dt/2 f(P*, phi*).  There src holds P*
+// and dst P^n, overwritten in place (each cell reads only its own).
 template <typename T>
-__global__ __launch_bounds__(256) void k_tdgl(const Inst<T> *I, Work w, int sel) {
-    const Blk b = find_block(w);
-    const Inst<T> &a = I[b.inst];
-    const GState *s = wstate(w, b.inst);
-    const int adv = s->adv;
-    if (!b.ok | ((sel != 0) & (adv == 0))) return;  // one exit test: see smooth_kernel
-    const int pcur = s->pcur;
-    const T3 t = split3(b.t, a.nx, a.ny);
+__device__ __forceinline__ void tdgl_tile(const Inst<T> &a, const GState *s, int tile, int src, int corr) {
+    const T3 t = split3(tile, a.nx, a.ny);
     const int i = t.tx * BX + threadIdx.x;
     const int j = t.ty * BY + threadIdx.y;
     const int k = a.f0 + t.tz;
     if (i >= a.nx || j >= a.ny) return;
     const size_t c = ((size_t)k * a.ny + j) * a.nx + i;
-    const double FX_AS(1) *P = asp<1>(a.P[pcur]);
+    const double FX_AS(1) *P = asp<1>(a.P[src]);
+    double FX_AS(1) *out = asp<1>(a.P[1 - src]);
     const double dF = tdgl_force(a, P, asp<1>(a.phi[s->cur]), i, j, k, c);
-    asp<1>(a.P[1 - pcur])[c] = P[c] - s->dt * a.Gamma * dF;
+    if (corr) out[c] = 0.5 * (out[c] + P[c]) - 0.5 * s->dt * a.Gamma * dF;
+    else out[c] = P[c] - s->dt * a.Gamma * dF;
 }
 
-// Corrector (Step 2a): P^{n+1} = P^n + dt/2 f(P^n, phi^n) + dt/2 f(P*, phi*); with
-// P* = P^n + dt f(P^n, phi^n) this is (P^n + P*)/2 + dt/2 f(P*, phi*).  P^n is
-// the other P buffer and is overwritten in place (each cell reads only its own).
+// A stand-alone Euler update of every instance (the P buffers are flipped after it).
 template <typename T>
-__global__ __launch_bounds__(256) void k_tdgl_corr(const Inst<T> *I, Work w) {
+__global__ __launch_bounds__(256) void k_tdgl(const Inst<T> *I, Work w) {
     const Blk b = find_block(w);
-    const Inst<T> &a = I[b.inst];
+    if (!b.ok) return;
     const GState *s = wstate(w, b.inst);
-    const int corr = s->corr;
-    if (!b.ok | (corr == 0)) return;  // one exit test: see smooth_kernel
-    const int pcur = s->pcur;
-    const T3 t = split3(b.t, a.nx, a.ny);
-    const int i = t.tx * BX + threadIdx.x;
-    const int j = t.ty * BY + threadIdx.y;
-    const int k = a.f0 + t.tz;
-    if (i >= a.nx || j >= a.ny) return;
-    const size_t c = ((size_t)k * a.ny + j) * a.nx + i;
-    const double FX_AS(1) *Ps = asp<1>(a.P[pcur]);
-    double FX_AS(1) *Pn = asp<1>(a.P[1 - pcur]);
-    const double dF = tdgl_force(a, Ps, asp<1>(a.phi[s->cur]), i, j, k, c);
-    Pn[c] = 0.5 * (Pn[c] + Ps[c]) - 0.5 * s->dt * a.Gamma * dF;
+    tdgl_tile(I[b.inst], s, b.t, s->pcur, 0);
 }
 
 // ------------------------------------------------------- solve bookkeeping
@@ -507,27 +493,15 @@ __global__ void k_flip(const Inst<T> *I, int ninst) {
     s->hist = 0;
 }
 
-// One thread per instance: start a solve.  sel = 1 (time step, instances
-// flagged by the advance slot): the TDGL update just written becomes the
-// current P, the gate potential comes from the run's schedule, and the
-// starting iterate may be extrapolated in time.  sel = 0: a plain solve of
-// every instance from its current phi.
+// Start a solve of one instance, its state in registers.  sel = 1 (time step, instances
+// flagged by the advance slot): the P update this slot computes becomes the current P, the
+// gate potential vg comes from the run's schedule (has_v), and the starting iterate may be
+// extrapolated in time.  sel = 0: a plain solve from its current phi.
 template <typename T>
-__global__ void k_begin(const Inst<T> *I, InstState *S, int ninst, int sel) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= ninst) return;
-    const Inst<T> &a = I[n];
-    GState *gs = asp<1>(S + n);                   // the state array itself (not through the
-                                                  // instance): one dependent load fewer
-    // read whole, updated in registers and written back once; an instance that
-    // starts no solve here is computed alike and not written back, so that no
-    // branch stands between the kernel's loads
-    InstState st = *(const InstState *)gs, *s = &st;
-    const bool run = !(sel && !s->adv && !s->corr);
+__device__ __forceinline__ void begin_solve(const Inst<T> &a, InstState *s, int sel, bool has_v, double vg) {
     if (sel) {
         s->pcur ^= 1;
-        const int q = s->step - s->sched_base;
-        if (s->adv && q >= 0 && q < s->sched_len) s->v_top = asp<1>(a.vsched)[q];
+        if (s->adv && has_v) s->v_top = vg;
     } else {
         s->phase = 0;
         s->pstar = -1;
@@ -542,18 +516,24 @@ __global__ void k_begin(const Inst<T> *I, InstState *S, int ninst, int sel) {
     else if (sel) order = min(s->hist - 1, a.warm) >= 2 ? min(s->hist - 1, a.warm) : 0;
     const int usestar = sel && s->adv && a.order2 && s->pstar >= 0;
     if (!usestar) s->pstar = -1;
-    int oth[2] = {0, 0}, no = 0;
-    for (int q = 0; q < a.nbuf && no < 2; ++q) {
-        bool used = q == s->cur || q == s->pstar;
+    int o0 = 0, o1 = 0, no = 0;
+#pragma unroll
+    for (int q = 0; q < kPhiBufs; ++q) {
+        bool used = q >= a.nbuf || q == s->cur || q == s->pstar;
 #pragma unroll
         for (int m = 0; m < kMaxHist; ++m) used |= m < s->hist && s->prev[m] == q;
-        if (!used) oth[no++] = q;
+        if (!used) {
+            if (no == 0) o0 = q;
+            else if (no == 1) o1 = q;
+            ++no;
+        }
     }
-    s->oth0 = oth[0];
-    s->oth1 = oth[1];
+    s->oth0 = o0;
+    s->oth1 = o1;
     s->order = order;
     s->usestar = usestar;
-    s->start = order > 0 || usestar ? oth[1] : s->cur;
+    const int cur = s->cur;
+    s->start = order > 0 || usestar ? o1 : cur;
     s->ts = sel;
     s->done = 0;
     s->cycles = 0;
@@ -561,57 +541,84 @@ __global__ void k_begin(const Inst<T> *I, InstState *S, int ninst, int sel) {
     s->fresh = 1;
     s->insolve = 1;
     s->light = 0;
-    if (run) *(InstState *)gs = st;
+}
+
+// One thread per instance: start the solves (after k_head in the first advance slot of a
+// run, or a plain solve of every instance).
+template <typename T>
+__global__ void k_begin(const Inst<T> *I, InstState *S, int ninst, int sel) {
+    const int n = blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= ninst) return;
+    const Inst<T> &a = I[n];
+    GState *gs = asp<1>(S + n);
+    InstState st = *(const InstState *)gs, *s = &st;
+    if (sel && !s->adv && !s->corr) return;
+    const int q = s->step - s->sched_base;
+    const bool has_v = sel && s->adv && q >= 0 && q < s->sched_len;
+    begin_solve(a, s, sel, has_v, has_v ? asp<1>(a.vsched)[q] : 0.0);
+    *(InstState *)gs = st;
 }
 
 // Lagrange extrapolation to t^{n+1} through t^n, t^{n-1}, ... (equal steps).
-__constant__ double kExtrapC[4][4] = {{1, 0, 0, 0}, {2, -1, 0, 0}, {3, -3, 1, 0}, {4, -6, 4, -1}};
+__device__ constexpr double kExtrapC[4][4] = {{1, 0, 0, 0}, {2, -1, 0, 0}, {3, -3, 1, 0}, {4, -6, 4, -1}};
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_extrap(const Inst<T> *I, Work w) {
-    const Blk b = find_block(w);
-    const Inst<T> &a = I[b.inst];
-    const GState *s = wstate(w, b.inst);
-    const int order = s->order, fresh = s->fresh, usestar = s->usestar;
-    if (!b.ok | (fresh == 0) | ((order == 0) & (usestar == 0))) return;  // one exit test: see smooth_kernel
-    const size_t nxy = (size_t)a.nx * a.ny, off = (size_t)a.kb * nxy, n = (size_t)a.nzd * nxy;
-    const double FX_AS(1) *in[4];
-    // newest level phi^n: the current iterate, or for a corrector the last stored level
-    const int sh = s->phase == 1 ? 1 : 0;
-    in[0] = asp<1>(a.phi[sh ? s->prev[0] : s->cur]) + off;
-    for (int q = 1; q <= order; ++q) in[q] = asp<1>(a.phi[s->prev[q - 1 + sh]]) + off;
-    double FX_AS(1) *out = asp<1>(a.phi[s->start]) + off;
-    const double FX_AS(1) *star = asp<1>(a.phi[s->usestar ? s->pstar : s->cur]) + off;
-    const size_t base = (size_t)b.t * kExtrapChunk;
-    const int tid = threadIdx.y * BX + threadIdx.x;
-    for (int q = 0; q < kExtrapChunk / 256; ++q) {
-        const size_t c = base + (size_t)q * 256 + tid;
-        if (c >= n) break;
-        double v = kExtrapC[order][0] * in[0][c];
-        for (int m = 1; m <= order; ++m) v += kExtrapC[order][m] * in[m][c];
-        if (s->usestar) v += star[c] - in[0][c];
-        out[c] = v;
+// Four cells per thread, every load ahead of the first store (the levels could alias the
+// output as far as the compiler knows, so a cell's store would hold up the next cell's loads).
+template <int ORD, int STAR>
+__device__ __forceinline__ void extrap_cells(const double FX_AS(1) *const (&in)[4], const double FX_AS(1) *star,
+                                             double FX_AS(1) *out, size_t base, size_t n) {
+    constexpr int U = kExtrapChunk / 256;
+    const size_t c0 = base + threadIdx.y * BX + threadIdx.x;
+    double x[ORD + 1][U], sv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const size_t c = min(c0 + 256 * u, n - 1);
+#pragma unroll
+        for (int m = 0; m <= ORD; ++m) x[m][u] = in[m][c];
+        if (STAR) sv[u] = star[c];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        double v = kExtrapC[ORD][0] * x[0][u];
+#pragma unroll
+        for (int m = 1; m <= ORD; ++m) v = fmad(kExtrapC[ORD][m], x[m][u], v);
+        if (STAR) v += sv[u] - x[0][u];
+        if (c0 + 256 * u < n) out[c0 + 256 * u] = v;
     }
 }
 
-// One thread per instance, first kernel of an advance slot (advance = 1) or
-// after a plain solve (advance = 0).  A solve that has stopped is finalized:
-// its last iterate becomes phi^{n+1} and, after a successful time step, phi^n
-// the newest stored level; the statistics and the status are recorded.
-// With advance set, an instance that is idle and below its run target (and
-// whose last solve succeeded) is flagged to start the next time step in this
-// slot; one that has reached the target or failed is parked.
 template <typename T>
-__global__ void k_head(const Inst<T> *I, InstState *S, int ninst, int advance) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= ninst) return;
-    // the state is read whole, updated in registers and written back once (one
-    // round trip instead of one per dependent field); the copies go through a generic
-    // view (the implicit copy operations take no address-space-qualified operand),
-    // which the compiler maps back to global loads and stores
-    GState *gs = asp<1>(S + n);
-    InstState st = *(const InstState *)gs, *s = &st;
-    const int order2 = I[n].order2;
+__device__ __forceinline__ void extrap_tile(const Inst<T> &a, const GState *s, int tile) {
+    const int order = s->order, usestar = s->usestar;
+    const size_t nxy = (size_t)a.nx * a.ny, off = (size_t)a.kb * nxy, n = (size_t)a.nzd * nxy;
+    // newest level phi^n: the current iterate, or for a corrector the last stored level
+    const int sh = s->phase == 1 ? 1 : 0;
+    const int cur = s->cur, pstar = s->pstar, start = s->start;
+    const int p0 = s->prev[0], p1 = s->prev[1], p2 = s->prev[2], p3 = s->prev[3];
+    const double FX_AS(1) *in[4] = {asp<1>(a.phi[sh ? p0 : cur]) + off, asp<1>(a.phi[sh ? p1 : p0]) + off,
+                                    asp<1>(a.phi[sh ? p2 : p1]) + off, asp<1>(a.phi[sh ? p3 : p2]) + off};
+    const double FX_AS(1) *star = asp<1>(a.phi[usestar ? pstar : cur]) + off;
+    double FX_AS(1) *out = asp<1>(a.phi[start]) + off;
+    const size_t base = (size_t)tile * kExtrapChunk;
+    if (usestar) {
+        if (order == 3) extrap_cells<3, 1>(in, star, out, base, n);
+        else if (order == 2) extrap_cells<2, 1>(in, star, out, base, n);
+        else if (order == 1) extrap_cells<1, 1>(in, star, out, base, n);
+        else extrap_cells<0, 1>(in, star, out, base, n);
+    } else {
+        if (order == 3) extrap_cells<3, 0>(in, star, out, base, n);
+        else if (order == 2) extrap_cells<2, 0>(in, star, out, base, n);
+        else extrap_cells<1, 0>(in, star, out, base, n);
+    }
+}
+
+// Finalize the solve of one instance (its state in registers) if it has stopped: its last
+// iterate becomes phi^{n+1} and, after a successful time step, phi^n the newest stored level;
+// the statistics and the status are recorded.  With advance set (an advance slot of a run),
+// an instance that is idle and below its run target (and whose last solve succeeded) is
+// flagged to start the next time step in this slot; one that has reached the target or
+// failed is parked.
+__device__ __forceinline__ void finish_solve(InstState *s, int order2, int advance) {
     int zf = 0, corr = 0, stepped = 0;
     if (s->insolve && s->done != 0) {
         const int c = s->cycles;
@@ -619,12 +626,16 @@ __global__ void k_head(const Inst<T> *I, InstState *S, int ninst, int advance) {
         s->total_cycles += c;
         s->max_cycles_step = max(s->max_cycles_step, c);
         s->insolve = 0;
+        s->v_done = s->v_top;
         if (s->done == 2) {                   // non-finite: keep phi^n, drop the history
             s->status = 5;
             s->failed += 1;
             s->hist = 0;
         } else {
-            const int fin = c == 0 ? s->start : ((c - 1) % 2 == 0 ? s->oth0 : s->oth1);
+            // plain values in the conditional: one of members yields a member's address, and
+            // an address taken keeps the whole state in scratch memory
+            const int i0 = s->start, o0 = s->oth0, o1 = s->oth1;
+            const int fin = c == 0 ? i0 : ((c - 1) % 2 == 0 ? o0 : o1);
             s->status = s->done == 1 ? 0 : 4;
             if (s->status != 0) s->failed += 1;
             const bool ok_step = s->ts && s->status == 0;
@@ -671,6 +682,21 @@ __global__ void k_head(const Inst<T> *I, InstState *S, int ninst, int advance) {
     s->adv = adv;
     s->corr = corr;
     s->stepped = stepped;
+}
+
+// The same as a launch of its own, one thread per instance (a plain solve's end, a run's
+// first advance slot).
+template <typename T>
+__global__ void k_head(const Inst<T> *I, InstState *S, int ninst, int advance) {
+    const int n = blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= ninst) return;
+    // the state is read whole, updated in registers and written back once (one
+    // round trip instead of one per dependent field); the copies go through a generic
+    // view (the implicit copy operations take no address-space-qualified operand),
+    // which the compiler maps back to global loads and stores
+    GState *gs = asp<1>(S + n);
+    InstState st = *(const InstState *)gs;
+    finish_solve(&st, I[n].order2, advance);
     *(InstState *)gs = st;
 }
 
@@ -682,38 +708,34 @@ __global__ void k_head(const Inst<T> *I, InstState *S, int ninst, int advance) {
 // Each block sums D and phi_int over a strided share of the face (fixed order), then
 // a tree in LDS; the finishing kernel adds the blocks' sums in block order.
 template <typename T>
-__global__ __launch_bounds__(256) void k_qv_part(const Inst<T> *I, int record) {
-    const int inst = blockIdx.x / kQvBlocks, blk = blockIdx.x % kQvBlocks;
-    const Inst<T> &a = I[inst];
-    const GState *s = asp<1>(a.st);
-    if (a.qv_kl < 0 || (record && !s->stepped)) return;
+__device__ __forceinline__ void qv_part_block(const Inst<T> &a, const GState *s, int blk, int pbuf, double (*red)[256]) {
+    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
     const size_t nxy = (size_t)a.nx * a.ny;
     const double FX_AS(1) *phL = asp<1>(a.phi[s->cur]) + (size_t)a.qv_kl * nxy;
     const double FX_AS(1) *phR = phL + nxy;
-    const double FX_AS(1) *Pfe = asp<1>(a.P[s->pcur]) + (size_t)(a.qv_kl + a.qv_fe_up) * nxy;
+    const double FX_AS(1) *Pfe = asp<1>(a.P[pbuf]) + (size_t)(a.qv_kl + a.qv_fe_up) * nxy;
     const double eL = a.qv_el, eR = a.qv_er, ih = 1.0 / a.h;
     const double ef = 2.0 * eL * eR / (eL + eR), wL = eR / (eL + eR), wR = eL / (eL + eR);
     const double hh_eL = 0.5 * a.h / eL;
     double sd = 0.0, sp = 0.0;
-    for (size_t c = (size_t)blk * 256 + threadIdx.x; c < nxy; c += (size_t)kQvBlocks * 256) {
+    for (size_t c = (size_t)blk * 256 + tid; c < nxy; c += (size_t)kQvBlocks * 256) {
         const double p = Pfe[c];
         const double pL = a.qv_fe_up ? 0.0 : p, pR = a.qv_fe_up ? p : 0.0;
         const double D = -ef * (phR[c] - phL[c]) * ih + wL * pL + wR * pR;
         sd += D;
         sp += phL[c] - (D - pL) * hh_eL;
     }
-    __shared__ double red[2][256];
-    red[0][threadIdx.x] = sd;
-    red[1][threadIdx.x] = sp;
+    red[0][tid] = sd;
+    red[1][tid] = sp;
     __syncthreads();
     for (int m = 128; m > 0; m >>= 1) {
-        if ((int)threadIdx.x < m) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + m];
-            red[1][threadIdx.x] += red[1][threadIdx.x + m];
+        if (tid < m) {
+            red[0][tid] += red[0][tid + m];
+            red[1][tid] += red[1][tid + m];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double FX_AS(1) *o = asp<1>(a.qv_part) + 2 * blk;
         o[0] = red[0][0];
         o[1] = red[1][0];
@@ -721,31 +743,65 @@ __global__ __launch_bounds__(256) void k_qv_part(const Inst<T> *I, int record) {
 }
 
 template <typename T>
-__global__ void k_qv_fin(const Inst<T> *I, int ninst, int record, double *out) {
+__global__ __launch_bounds__(256) void k_qv_part(const Inst<T> *I) {
+    __shared__ double red[2][256];
+    const Inst<T> &a = I[blockIdx.x / kQvBlocks];
+    const GState *s = asp<1>(a.st);
+    if (a.qv_kl < 0) return;
+    qv_part_block(a, s, blockIdx.x % kQvBlocks, s->pcur, red);
+}
+
+// Q and V_fe from the face sums, with gate potential vt.
+template <typename T>
+__device__ __forceinline__ void qv_finish(const Inst<T> &a, double vt, double &Q, double &V) {
+    double sd = 0.0, sp = 0.0;
+    const double FX_AS(1) *p = asp<1>(a.qv_part);
+    for (int b = 0; b < kQvBlocks; ++b) { sd += p[2 * b]; sp += p[2 * b + 1]; }
+    const double area = (double)a.nx * a.ny;
+    Q = -sd / area;
+    V = vt - sp / area;
+}
+
+template <typename T>
+__global__ void k_qv_fin(const Inst<T> *I, int ninst, double *out) {
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= ninst) return;
     const Inst<T> &a = I[n];
-    const GState *s = asp<1>(a.st);
-    if (record && (a.qv_kl < 0 || !s->stepped)) return;
     double Q = __builtin_nan(""), V = __builtin_nan("");
-    if (a.qv_kl >= 0) {
-        double sd = 0.0, sp = 0.0;
-        const double FX_AS(1) *p = asp<1>(a.qv_part);
-        for (int b = 0; b < kQvBlocks; ++b) { sd += p[2 * b]; sp += p[2 * b + 1]; }
-        const double area = (double)a.nx * a.ny;
-        Q = -sd / area;
-        V = s->v_top - sp / area;
-    }
-    if (record) {
-        const int q = s->step - 1 - s->sched_base;
-        if (q >= 0 && q < kRecSteps) {
-            double FX_AS(1) *r = asp<1>(a.qv_rec) + 2 * q;
-            r[0] = Q;
-            r[1] = V;
-        }
-    } else {
-        asp<1>(out)[2 * n] = Q;
-        asp<1>(out)[2 * n + 1] = V;
+    if (a.qv_kl >= 0) qv_finish(a, asp<1>(a.st)->v_top, Q, V);
+    asp<1>(out)[2 * n] = Q;
+    asp<1>(out)[2 * n + 1] = V;
+}
+
+// The field work of an advance slot, after the states have moved on: the TDGL update (Euler or
+// corrector) of the instances whose P buffers were flipped, the starting iterate of the
+// solves just begun, and, when a run records Q and V_fe, the face sums of the steps just
+// completed (their P is the buffer the flip left behind).  The three parts read and write
+// different buffers, so they can share a launch.  Grid: gt blocks of TDGL tiles, ge of
+// extrapolation tiles, the rest face sums; PART names the parts a launch holds (1 TDGL, 2 the
+// others, 3 all): see launch_fields.
+template <typename T, int PART>
+__global__ __launch_bounds__(256) void k_fields(const Inst<T> *I, Work wt, Work we, int gt, int ge) {
+    __shared__ double red[2][256];
+    const int bx = blockIdx.x;
+    if ((PART & 1) && bx < gt) {
+        const Blk b = find_block(wt, bx, gt);
+        const GState *s = wstate(wt, b.inst);
+        const int adv = s->adv, corr = s->corr;
+        if (!b.ok | ((adv == 0) & (corr == 0))) return;  // one exit test: see smooth_kernel
+        tdgl_tile(I[b.inst], s, b.t, 1 - s->pcur, corr);
+    } else if ((PART & 2) && bx < gt + ge) {
+        const Blk b = find_block(we, bx - gt, ge);
+        const GState *s = wstate(we, b.inst);
+        const int order = s->order, fresh = s->fresh, usestar = s->usestar;
+        if (!b.ok | (fresh == 0) | ((order == 0) & (usestar == 0))) return;
+        extrap_tile(I[b.inst], s, b.t);
+    } else if (PART & 2) {
+        const int q = bx - gt - ge, inst = q / kQvBlocks;
+        const Inst<T> &a = I[inst];
+        const GState *s = asp<1>(wt.st + inst);
+        if ((a.qv_kl < 0) | (s->stepped == 0)) return;
+        qv_part_block(a, s, q % kQvBlocks, s->adv ? 1 - s->pcur : s->pcur, red);
     }
 }
 
@@ -946,24 +1002,35 @@ __global__ __launch_bounds__(256) void k_residual(const Inst<T> *I, Work w, int 
 // instance) and its stop decision.  f = 0 exactly with a nonzero residual: N(0) = 0,
 // so phi = 0 is the root; the block sets the solve's last iterate to it at once
 // (the slot that finalizes the solve reads that buffer as phi^{n+1}).
-template <typename T, int CC>
-__global__ __launch_bounds__(1024) void k_reduce(const Inst<T> *I, InstState *S) {
+// MODE 0: the residual of a solve's starting iterate; with rec the block also writes the
+// (Q, V_fe) record of the step completed in this slot.  MODE 1: after a cycle.  MODE 2: after
+// a cycle of a run; the block then finalizes the solve if it has stopped and starts the
+// instance's next one, all on the state in thread 0's registers (launches of their own for
+// these single-thread steps cost a gap of the stream each).
+template <typename T, int MODE>
+__global__ __launch_bounds__(1024) void k_reduce(const Inst<T> *I, InstState *S, int rec) {
     __shared__ double lr[16];
     __shared__ double lf[16];
     __shared__ int lz;
     const Inst<T> &a = I[blockIdx.x];
-    GState *s = asp<1>(S + blockIdx.x);
+    GState *gs = asp<1>(S + blockIdx.x);
     // the state and the partials are read together, the partials two per thread at a
     // time, so that the block waits on memory once for them (an instance that is not
     // reduced here ignores what it read); each thread still adds its partials in
     // index order
     const double FX_AS(1) *part = asp<1>(a.part);
-    const bool skip = CC ? s->done != 0 : !s->fresh;
-    // what the stop decision reads, fetched with the rest
-    const double x_prev = s->rn2, tol2 = a.tol2, light_r2 = a.light_r2, light_c2 = a.light_c2;
-    const int cycles = s->cycles + (CC ? 1 : 0), max_cycles = a.max_cycles, light_ok = a.light_ok;
-    // the solve's last iterate: the start before any cycle, else the latest cycle's output
-    const int fin = cycles == 0 ? s->start : ((cycles - 1) % 2 == 0 ? s->oth0 : s->oth1);
+    const bool skip = MODE ? gs->done != 0 : !gs->fresh;
+    InstState st = *(const InstState *)gs, *s = &st;
+    const double tol2 = a.tol2, light_r2 = a.light_r2, light_c2 = a.light_c2;
+    const int max_cycles = a.max_cycles, light_ok = a.light_ok;
+    // gate potentials of the step in progress and of the one after it
+    const int q0 = s->step - s->sched_base, qn = s->sched_len;
+    double v0 = 0.0, v1 = 0.0;
+    if (MODE == 2 && threadIdx.x == 0) {
+        const double FX_AS(1) *vs = asp<1>(a.vsched);
+        v0 = vs[q0 >= 0 && q0 < qn ? q0 : 0];
+        v1 = vs[q0 + 1 >= 0 && q0 + 1 < qn ? q0 + 1 : 0];
+    }
     const int n = tiles3(a.nx, a.ny, (a.nzd + kResZ - 1) / kResZ);
     const int B = blockDim.x;
     double r = 0.0, f = 0.0;
@@ -977,32 +1044,65 @@ __global__ __launch_bounds__(1024) void k_reduce(const Inst<T> *I, InstState *S)
         f += f1;
     }
     if (q < n) { r += part[2 * q]; f += part[2 * q + 1]; }
-    if (skip) return;
+    if (MODE == 0 && rec && threadIdx.x == 0 && a.qv_kl >= 0 && s->stepped) {
+        const int qr = s->step - 1 - s->sched_base;
+        if (qr >= 0 && qr < kRecSteps) {
+            double Q, V;
+            qv_finish(a, s->v_done, Q, V);
+            double FX_AS(1) *o = asp<1>(a.qv_rec) + 2 * qr;
+            o[0] = Q;
+            o[1] = V;
+        }
+    }
+    if (MODE != 2 && skip) return;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) { r += __shfl_down(r, off, 64); f += __shfl_down(f, off, 64); }
     if ((threadIdx.x & 63) == 0) { lr[threadIdx.x >> 6] = r; lf[threadIdx.x >> 6] = f; }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double x = 0.0, y = 0.0;
-        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) { x += lr[q]; y += lf[q]; }
-        s->rn2 = x;
-        s->fn2 = y;
-        s->fresh = 0;
-        if (CC) s->cycles = cycles;
         int zb = -1;
-        if (!isfinite(x) || !isfinite(y)) s->done = 2;
-        else if (y == 0.0) {
-            s->done = 1;
-            s->zpend = x != 0.0;
-            if (x != 0.0) zb = fin;
+        if (!skip) {
+            double x = 0.0, y = 0.0;
+            for (int u = 0; u < (int)(blockDim.x >> 6); ++u) { x += lr[u]; y += lf[u]; }
+            const double x_prev = s->rn2;
+            const int cycles = s->cycles + (MODE ? 1 : 0);
+            // the solve's last iterate: the start before any cycle, else the latest cycle's output
+            const int i0 = s->start, out0 = s->oth0, out1 = s->oth1;
+            const int fin = cycles == 0 ? i0 : ((cycles - 1) % 2 == 0 ? out0 : out1);
+            s->rn2 = x;
+            s->fn2 = y;
+            s->fresh = 0;
+            s->cycles = cycles;
+            if (!isfinite(x) || !isfinite(y)) s->done = 2;
+            else if (y == 0.0) {
+                s->done = 1;
+                s->zpend = x != 0.0;
+                if (x != 0.0) zb = fin;
+            }
+            else if (x <= tol2 * y || x == 0.0) s->done = 1;
+            else if (cycles >= max_cycles) s->done = 3;
+            // within kLightRatio of the tolerance, after a cycle that contracted the
+            // residual at least kLightContraction-fold (the linear regime, as in a
+            // time step's first cycle), one V(1,1)-like cycle (contraction about 0.2)
+            // finishes the solve at a little over half the cost
+            s->light = light_ok && MODE && x <= light_r2 * tol2 * y && x * light_c2 <= x_prev;
         }
-        else if (x <= tol2 * y || x == 0.0) s->done = 1;
-        else if (cycles >= max_cycles) s->done = 3;
-        // within kLightRatio of the tolerance, after a cycle that contracted the
-        // residual at least kLightContraction-fold (the linear regime, as in a
-        // time step's first cycle), one V(1,1)-like cycle (contraction about 0.2)
-        // finishes the solve at a little over half the cost
-        s->light = light_ok && CC && x <= light_r2 * tol2 * y && x * light_c2 <= x_prev;
+        if (MODE == 2) {
+            finish_solve(s, a.order2, 1);
+            if (s->adv || s->corr) {
+                const int qs = s->step - s->sched_base;
+                begin_solve(a, s, 1, qs >= 0 && qs < qn, qs == q0 ? v0 : v1);
+            }
+            *(InstState *)gs = st;
+        } else {
+            gs->rn2 = s->rn2;
+            gs->fn2 = s->fn2;
+            gs->fresh = 0;
+            gs->cycles = s->cycles;
+            gs->done = s->done;
+            gs->zpend = s->zpend;
+            gs->light = s->light;
+        }
         lz = zb;
     }
     __syncthreads();
@@ -2508,20 +2608,32 @@ __global__ void k_fill(double *x, size_t n, double v) {
     } while (0)
 
 template <typename T>
-void launch_tdgl(const Inst<T> *I, const Work &w, int sel, hipStream_t st) {
-    FX_LAUNCH(k_tdgl<T>, w, I, w, sel);
+void launch_tdgl(const Inst<T> *I, const Work &w, hipStream_t st) {
+    FX_LAUNCH(k_tdgl<T>, w, I, w);
 }
+
+// One launch on small problems, where a launch costs more than its work; from about 2^21 device
+// cells two, each with its own register budget (shared, the TDGL tiles run at the
+// extrapolation's lower occupancy: 256 x 256 x 120 cells took 84 us together and 75 us apart,
+// 128 x 128 x 48 cells 8.3 us together and 11.1 us apart).
 template <typename T>
-void launch_tdgl_corr(const Inst<T> *I, const Work &w, hipStream_t st) {
-    FX_LAUNCH(k_tdgl_corr<T>, w, I, w);
+void launch_fields(const Inst<T> *I, const Work &wt, const Work &we, int rec, hipStream_t st) {
+    const int gt = wt.total > 0 ? (int)grid_of(wt.total).x : 0, ge = (int)grid_of(we.total).x;
+    const int gq = rec ? wt.ninst * kQvBlocks : 0;
+    if (we.total < (1 << 21) / kExtrapChunk) {
+        hipLaunchKernelGGL((k_fields<T, 3>), dim3(gt + ge + gq), dim3(BX, BY), 0, st, I, wt, we, gt, ge);
+        return;
+    }
+    if (gt) hipLaunchKernelGGL((k_fields<T, 1>), dim3(gt), dim3(BX, BY), 0, st, I, wt, we, gt, 0);
+    hipLaunchKernelGGL((k_fields<T, 2>), dim3(ge + gq), dim3(BX, BY), 0, st, I, wt, we, 0, ge);
 }
 
 inline dim3 per_inst(int ninst) { return dim3((ninst + 63) / 64); }
 
 template <typename T>
-void launch_qv(const Inst<T> *I, int ninst, int record, double *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_qv_part<T>, dim3(ninst * kQvBlocks), dim3(256), 0, st, I, record);
-    hipLaunchKernelGGL(k_qv_fin<T>, per_inst(ninst), dim3(64), 0, st, I, ninst, record, out);
+void launch_qv(const Inst<T> *I, int ninst, double *out, hipStream_t st) {
+    hipLaunchKernelGGL(k_qv_part<T>, dim3(ninst * kQvBlocks), dim3(256), 0, st, I);
+    hipLaunchKernelGGL(k_qv_fin<T>, per_inst(ninst), dim3(64), 0, st, I, ninst, out);
 }
 
 template <typename T>
@@ -2535,11 +2647,6 @@ void launch_begin(const Inst<T> *I, InstState *S, int ninst, int sel, hipStream_
 }
 
 template <typename T>
-void launch_extrap(const Inst<T> *I, const Work &w, hipStream_t st) {
-    FX_LAUNCH(k_extrap<T>, w, I, w);
-}
-
-template <typename T>
 void launch_residual(const Inst<T> *I, const ResWork &w, int after_cycle, int any_fd, hipStream_t st) {
     auto *k0 = any_fd ? &k_residual<T, 0, 1> : &k_residual<T, 0, 0>;
     auto *k2 = any_fd ? &k_residual<T, 2, 1> : &k_residual<T, 2, 0>;
@@ -2548,9 +2655,9 @@ void launch_residual(const Inst<T> *I, const ResWork &w, int after_cycle, int an
 }
 
 template <typename T>
-void launch_reduce(const Inst<T> *I, InstState *S, int ninst, int count_cycle, hipStream_t st) {
-    if (count_cycle) hipLaunchKernelGGL((k_reduce<T, 1>), dim3(ninst), dim3(1024), 0, st, I, S);
-    else hipLaunchKernelGGL((k_reduce<T, 0>), dim3(ninst), dim3(1024), 0, st, I, S);
+void launch_reduce(const Inst<T> *I, InstState *S, int ninst, int mode, int rec, hipStream_t st) {
+    auto *k = mode == 2 ? &k_reduce<T, 2> : mode == 1 ? &k_reduce<T, 1> : &k_reduce<T, 0>;
+    hipLaunchKernelGGL(k, dim3(ninst), dim3(1024), 0, st, I, S, rec);
 }
 
 template <typename T, int ZT>
@@ -2674,14 +2781,13 @@ void launch_fill(double *x, size_t n, double v, hipStream_t st) {
 }
 
 #define FX_INST(T)                                                                                           \
-    template void launch_tdgl<T>(const Inst<T> *, const Work &, int, hipStream_t);                           \
-    template void launch_tdgl_corr<T>(const Inst<T> *, const Work &, hipStream_t);                           \
+    template void launch_tdgl<T>(const Inst<T> *, const Work &, hipStream_t);                                \
+    template void launch_fields<T>(const Inst<T> *, const Work &, const Work &, int, hipStream_t);           \
     template void launch_flip<T>(const Inst<T> *, int, hipStream_t);                                        \
-    template void launch_qv<T>(const Inst<T> *, int, int, double *, hipStream_t);                            \
+    template void launch_qv<T>(const Inst<T> *, int, double *, hipStream_t);                                 \
     template void launch_begin<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                                  \
-    template void launch_extrap<T>(const Inst<T> *, const Work &, hipStream_t);                              \
     template void launch_residual<T>(const Inst<T> *, const ResWork &, int, int, hipStream_t);                    \
-    template void launch_reduce<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                                  \
+    template void launch_reduce<T>(const Inst<T> *, InstState *, int, int, int, hipStream_t);                \
     template void launch_smooth<T>(const Inst<T> *, const Work &, int, int, int, int, const SmoothCfg &,     \
                                    double *, hipStream_t, hipEvent_t, hipEvent_t, int);                      \
     template void launch_smooth_zpair<T>(const Inst<T> *, const Work &, int, const SmoothCfg &, hipStream_t); \

@@ -937,32 +937,29 @@ void enq_vcycle(Engine *e) {
     }
 }
 
-// Cycle slot: one cycle and its residual for every running solve.
+// Cycle slot: one cycle and its residual for every running solve.  In a run (run = 1) the
+// norm reduction also moves the states on: it finalizes stopped solves and starts the next
+// time step where due.
 template <typename T>
-void enq_cycle(Engine *e) {
+void enq_cycle(Engine *e, int run) {
     enq_vcycle<T>(e);
     launch_residual(idev<T>(e), e->w_res, 1, e->any_fd, e->st);
-    launch_reduce(idev<T>(e), e->st_dev, e->n, 1, e->st);
+    launch_reduce(idev<T>(e), e->st_dev, e->n, run ? 2 : 1, 0, e->st);
 }
 
-// Advance slot: finalize stopped solves, start the next time step where due.
+// Advance slot, after the states have moved on: the fields of the steps just started.
 template <typename T>
 void enq_advance(Engine *e) {
     const Inst<T> *I = idev<T>(e);
-    launch_head(I, e->st_dev, e->n, 1, e->st);
-    if (e->rec) launch_qv(I, e->n, 1, nullptr, e->st);
-    launch_tdgl(I, e->w_tdgl, 1, e->st);
-    if (e->any_order2) launch_tdgl_corr(I, e->w_tdgl, e->st);
-    launch_begin(I, e->st_dev, e->n, 1, e->st);
-    launch_extrap(I, e->w_ext, e->st);
+    launch_fields(I, e->w_tdgl, e->w_ext, e->rec, e->st);
     launch_residual(I, e->w_res, 0, e->any_fd, e->st);
-    launch_reduce(I, e->st_dev, e->n, 0, e->st);
+    launch_reduce(I, e->st_dev, e->n, 0, e->rec, e->st);
 }
 
 template <typename T>
 void enq_units(Engine *e, int units) {
     for (int u = 0; u < units; ++u) {
-        enq_cycle<T>(e);
+        enq_cycle<T>(e, 1);
         enq_advance<T>(e);
     }
 }
@@ -1023,12 +1020,12 @@ fx_status solve_plain_t(Engine *e) {
     const Inst<T> *I = idev<T>(e);
     launch_begin(I, e->st_dev, e->n, 0, e->st);
     launch_residual(I, e->w_res, 0, e->any_fd, e->st);
-    launch_reduce(I, e->st_dev, e->n, 0, e->st);
+    launch_reduce(I, e->st_dev, e->n, 0, 0, e->st);
     int enq = 0;
     int batch = e->trace ? 0 : std::max(1, e->k_pred);
     fx_status st;
     for (;;) {
-        for (int q = 0; q < batch && enq < e->max_cycles; ++q, ++enq) enq_cycle<T>(e);
+        for (int q = 0; q < batch && enq < e->max_cycles; ++q, ++enq) enq_cycle<T>(e, 0);
         if ((st = read_states(e))) return st;
         bool all = true;
         for (int i = 0; i < e->n; ++i) all &= e->mir[i].done != 0;
@@ -1078,6 +1075,8 @@ fx_status run_t(Engine *e, int nsteps, double dt, const double *const *sched, do
                                       hipMemcpyHostToDevice, e->st));
         }
         launch_run_setup(I, e->n, chunk, sched ? 1 : 0, dt, first, e->st);
+        launch_head(I, e->st_dev, e->n, 1, e->st);
+        launch_begin(I, e->st_dev, e->n, 1, e->st);
         enq_advance<T>(e);
         long long budget = (long long)chunk * (e->any_order2 ? 2 : 1) * (e->max_cycles + 1) + 1;
         int units = std::min(e->ucap, chunk);
@@ -1136,8 +1135,8 @@ bool has_interface(const InstHost &h) {
 
 // Q and V_fe of every instance's current state into host arrays of n entries.
 fx_status qv_now(Engine *e, double *h_Q, double *h_V) {
-    if (e->prec == FX_PREC_MIXED) launch_qv(idev<float>(e), e->n, 0, e->qv_out, e->st);
-    else launch_qv(idev<double>(e), e->n, 0, e->qv_out, e->st);
+    if (e->prec == FX_PREC_MIXED) launch_qv(idev<float>(e), e->n, e->qv_out, e->st);
+    else launch_qv(idev<double>(e), e->n, e->qv_out, e->st);
     std::vector<double> b(2 * (size_t)e->n);
     HIP_OK(hipMemcpyAsync(b.data(), e->qv_out, b.size() * sizeof(double), hipMemcpyDeviceToHost, e->st));
     HIP_OK(hipStreamSynchronize(e->st));
@@ -1756,10 +1755,10 @@ fx_status tdgl_step(fx_stack *s, double dt) {
     e->mir[0].dt = dt;
     put_state(e, 0);
     if (e->prec == FX_PREC_MIXED) {
-        launch_tdgl(idev<float>(e), e->w_tdgl, 0, e->st);
+        launch_tdgl(idev<float>(e), e->w_tdgl, e->st);
         launch_flip(idev<float>(e), 1, e->st);
     } else {
-        launch_tdgl(idev<double>(e), e->w_tdgl, 0, e->st);
+        launch_tdgl(idev<double>(e), e->w_tdgl, e->st);
         launch_flip(idev<double>(e), 1, e->st);
     }
     e->mir[0].pcur ^= 1;
