@@ -55,12 +55,25 @@ constexpr int kPhiBufs = 8;       // phi^n, up to 3 stored levels, two iterate b
                                   // the last predictor's phi*
 constexpr int kMaxHist = 4;       // stored levels of a predictor-corrector instance (Euler: 3)
 constexpr int kCoarseLdsBytes = 64 * 1024;
-// temporal blocking of the smoothing below the finest level (k_pre_tb / k_post_tb)
+// temporal blocking of the smoothing (k_pre_tb / k_post_tb)
 constexpr int kTbT = 8;                    // tile edge (cells)
 constexpr int kTbH = 4;                    // ring (cells): 2 nu for nu <= 2 sweeps
-constexpr int kTbW = kTbT + 2 * kTbH;      // box edge; a thread per box column
-constexpr int kTbMaxNz = 30;               // planes of a blocked level (a column's values in registers)
-constexpr int kTbLdsBytes = 64 * 1024;     // largest box (all planes of a level) and its tables
+constexpr int kTbW = kTbT + 2 * kTbH;      // box edge
+constexpr int kTbShares = 4;               // shares of the planes: a thread per box column and share
+constexpr int kTbMaxNz = 64;               // planes of a blocked level
+// cells of one colour per thread, for levels of at most nz planes
+__host__ __device__ constexpr int tb_zq(int nz) {
+    const int q = ((nz + 1) / 2 + kTbShares - 1) / kTbShares;
+    return q <= 4 ? q : (q <= 6 ? 6 : 8);
+}
+// LDS of a box of nz planes (and two of padding), of the nzc coarse planes under it in the post
+// launch, and of a value per plane; 64 planes and 32 coarse ones of doubles take 157.5 of a
+// workgroup's 160 KB
+__host__ __device__ constexpr size_t tb_lds_bytes(int nz, int nzc, size_t w) {
+    return ((size_t)((nz > 2 * tb_zq(nz) ? nz : 2 * tb_zq(nz)) + 2) * kTbW * kTbW +
+            (size_t)nzc * (kTbW / 2 + 2) * (kTbW / 2 + 2) + nz) * w;
+}
+static_assert(tb_lds_bytes(kTbMaxNz, kTbMaxNz / 2, sizeof(double)) <= 160 * 1024, "a workgroup's LDS");
 constexpr int kQvBlocks = 8;      // blocks per instance of the interface-plane reductions
 constexpr int kRecSteps = 1024;   // recorded steps per instance held on the device
 
@@ -119,7 +132,7 @@ struct LevelArgs {
     T *r;
     T *sig;
     int sig_lo, sig_hi;
-    T *ealt;                         // black values between the blocked pre- and post-smoothing (or null)
+    T *ealt;                         // black values between the blocked pre- and post-smoothing
 };
 
 // Transfer tables between a level and the next coarser one.
@@ -239,9 +252,10 @@ template <typename T> void launch_prolong(const Inst<T> *I, const Work &w, int l
 template <typename T> void launch_prolong_cc(const Inst<T> *I, const Work &w, int level, int cz, hipStream_t st);
 template <typename T> void launch_coarse(const Inst<T> *I, InstState *S, int ninst, int lds_bytes, hipStream_t st);
 // pre-smoothing (nu zero-start sweeps) + restriction of level `level`, and prolongation +
-// post-smoothing (nu sweeps), a block per kTbT x kTbT tile with lds_bytes of LDS
-template <typename T> void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int lds_bytes, hipStream_t st);
-template <typename T> void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int lds_bytes, hipStream_t st);
+// post-smoothing (nu sweeps; on the finest level with the Newton update), a block per kTbT x kTbT
+// tile; nz, nzc: the most planes of an instance on this level and the next
+template <typename T> void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, hipStream_t st);
+template <typename T> void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, int nzc, hipStream_t st);
 template <typename T> void launch_head(const Inst<T> *I, InstState *S, int ninst, int advance, hipStream_t st);
 template <typename T> void launch_run_setup(const Inst<T> *I, int ninst, int nsteps, int has_sched, double dt,
                                             int first, hipStream_t st);

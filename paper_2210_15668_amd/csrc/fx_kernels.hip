@@ -176,12 +176,20 @@ __device__ __forceinline__ typename V::value_type diag_of(const V &L, int i, int
     return d;
 }
 
-// Gauss-Seidel update of one cell of (L + diag sigma) e = r.
+// Gauss-Seidel update of one cell of (L + diag sigma) e = r.  Every smoother forms a value as
+// (r + neighbour sum) times the reciprocal of the diagonal: the kernels that hold a level in LDS
+// form the reciprocal once for all sweeps, and the others round alike (the product stays a
+// product where its value feeds a sum in the same thread: no contraction).
+template <typename T>
+__device__ __forceinline__ T gs_value(T rhs, T diag) {
+#pragma clang fp contract(off)
+    return rhs * (T(1) / diag);
+}
 template <typename V>
 __device__ __forceinline__ void gs_cell(const V &L, int i, int j, int k, int zero_init) {
     const int c = cidx(L, i, j, k);
     const auto d = diag_of(L, i, j, k);
-    L.e[c] = zero_init ? L.r[c] / d : (L.r[c] + nb_sum(L, L.e, i, j, k)) / d;
+    L.e[c] = gs_value(zero_init ? L.r[c] : L.r[c] + nb_sum(L, L.e, i, j, k), d);
 }
 
 // Colour of a cell on a plainly stored level (odd x or y extent).  With an
@@ -241,6 +249,27 @@ __device__ __forceinline__ void restrict_cell(const V &F, const V &C, const X &X
     else restrict_cell_t<0>(F, C, Xf, I, J, K);
 }
 
+// Fused multiply-add of the working precision, written out so that every kernel that
+// interpolates rounds alike whatever the compiler would contract.
+__device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// Neighbour sum of a red/black cell from the other colour's six values; cx, cy (0 for a single
+// row), cm and cp (0 at the contacts) weigh the x, y, lower and upper neighbours.  With the red
+// residual below one expression shared by every kernel, so that they round alike.
+template <typename T>
+__device__ __forceinline__ T nb6(T cx, T cy, T cm, T cp, T ex0, T ex1, T ey0, T ey1, T ez0, T ez1) {
+    return fmad(cp, ez1, fmad(cm, ez0, fmad(cy, ey0 + ey1, cx * (ex0 + ex1))));
+}
+template <typename T, int AS>
+__device__ __forceinline__ T rb_nb_sum(const Lv<T, AS> &L, int k, T ex0, T ex1, T ey0, T ey1, T ez0, T ez1) {
+    const T cx = L.cxy[k];
+    return nb6(cx, L.ny > 1 ? cx : T(0), k > 0 ? L.czm[k] : T(0), k < L.nz - 1 ? L.czp[k] : T(0), ex0, ex1, ey0, ey1, ez0,
+               ez1);
+}
+template <typename T>
+__device__ __forceinline__ T res_value(T r, T diag, T e, T nb) { return r - fmad(diag, e, -nb); }
+
 // The same restriction for a red/black level halved in x and y, in global
 // memory, with every load issued before any arithmetic: in each child row the
 // red child is the one with dx = (dy + k) & 1, a coarse plane with a single
@@ -295,26 +324,17 @@ __device__ __forceinline__ void restrict_cell_rbxy(const V &F, const V &C, const
 #pragma unroll
             for (int dx = 0; dx < 2; ++dx) {
                 const T sgc = hs ? sg[dz][dy][dx] : T(0);
-                ss += wz * (double)sgc;
+                ss = fmad(wz, (double)sgc, ss);
                 if (dx != ((dy + k) & 1)) continue;
-                T nbs = 0;
-                nbs += cx[dz] * (nb[dz][dy][0] + nb[dz][dy][1]);
-                nbs += cx[dz] * (nb[dz][dy][2] + nb[dz][dy][3]);
-                if (k > 0) nbs += czm[dz] * nb[dz][dy][4];
-                if (k < F.nz - 1) nbs += czp[dz] * nb[dz][dy][5];
-                const T res = rv[dz][dy] - ((dg[dz] + sgc) * ev[dz][dy] - nbs);
-                sr += wz * (double)res;
+                const T nbs = nb6(cx[dz], cx[dz], k > 0 ? czm[dz] : T(0), k < F.nz - 1 ? czp[dz] : T(0), nb[dz][dy][0],
+                                  nb[dz][dy][1], nb[dz][dy][2], nb[dz][dy][3], nb[dz][dy][4], nb[dz][dy][5]);
+                sr = fmad(wz, (double)res_value(rv[dz][dy], dg[dz] + sgc, ev[dz][dy], nbs), sr);
             }
         }
     }
     C.r[cidx(C, I, J, K)] = (T)(sr * 0.25);
     if (has_sig(C, K)) C.sig[sidx(C, I, J, K)] = (T)(ss * 0.25);
 }
-
-// Fused multiply-add of the working precision, written out so that every kernel that
-// interpolates rounds alike whatever the compiler would contract.
-__device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // The lateral interpolant of one coarse plane: sum of w[yy][xx] v[yy][xx] in row order,
 // the first term a product and the others fused multiply-adds.  With lint_z, the value
@@ -1115,17 +1135,6 @@ __global__ __launch_bounds__(1024) void k_reduce(const Inst<T> *I, InstState *S,
 }
 
 // ----------------------------------------------------------------- smoother
-// Neighbour sum of a red/black cell from the other colour's six values (the
-// z terms vanish on the contact planes); one expression shared by every kernel
-// that updates a cell, so that they round alike.
-template <typename T, int AS>
-__device__ __forceinline__ T rb_nb_sum(const Lv<T, AS> &L, int k, T ex0, T ex1, T ey0, T ey1, T ez0, T ez1) {
-    const T cx = L.cxy[k];
-    const T cy = L.ny > 1 ? cx : T(0);
-    return cx * (ex0 + ex1) + cy * (ey0 + ey1) + (k > 0 ? L.czm[k] : T(0)) * ez0 +
-           (k < L.nz - 1 ? L.czp[k] : T(0)) * ez1;
-}
-
 // One colour of red-black Gauss-Seidel on (L + diag sigma) e = r.  Split
 // storage: a thread per cell of that colour, ZT planes per thread with all
 // loads issued first; plainly stored levels: a thread per cell and ZT planes
@@ -1191,7 +1200,7 @@ __device__ __forceinline__ void smooth_rb_body(const Inst<T> &a, const GState *s
         const bool hs = k >= L.sig_lo && k < L.sig_hi;
         T acc = 0;
         if (!ZI) acc = rb_nb_sum(L, k, ex0[z], ex1[z], ey0[z], ey1[z], ez0[z], ez1[z]);
-        out[z] = (rr[z] + acc) / (L.dg[k] + (hs ? sg[z] : T(0)));
+        out[z] = gs_value(rr[z] + acc, L.dg[k] + (hs ? sg[z] : T(0)));
     }
     // Stores outside branches: a lane past the row end works on cell (0, 0) and a slot past
     // the top on plane nz - 1, from the same inputs as the lane owning that cell, so its store
@@ -1258,7 +1267,7 @@ __device__ __forceinline__ void smooth_zpair_body(const Lv<T, 1> &L, int t, int 
     auto red = [&](int c, int kk) {
         const bool hs = kk >= L.sig_lo && kk < L.sig_hi;
         const T sg = L.sig[hs ? (kk - L.sig_lo) * plane + (c - kk * plane) : 0];
-        return (r_red[c] + T(0)) / (L.dg[kk] + (hs ? sg : T(0)));
+        return gs_value(r_red[c] + T(0), L.dg[kk] + (hs ? sg : T(0)));
     };
 #pragma unroll
     for (int z = 0; z < ZT; ++z) {
@@ -1276,7 +1285,7 @@ __device__ __forceinline__ void smooth_zpair_body(const Lv<T, 1> &L, int t, int 
         const T ez0 = k > 0 ? red(q - plane, k - 1) : red(q, k);
         const T ez1 = k < L.nz - 1 ? red(q + plane, k + 1) : red(q, k);
         const T acc = rb_nb_sum(L, k, ex0, ex1, ey0, ey1, ez0, ez1);
-        e_blk[q] = (rb + acc) / (L.dg[k] + (hs ? sb : T(0)));
+        e_blk[q] = gs_value(rb + acc, L.dg[k] + (hs ? sb : T(0)));
         e_red[q] = (i & 1) ? ex1 : ex0;                  // the pair's red cell: x - 1 or x + 1
     }
 }
@@ -1419,7 +1428,7 @@ __device__ __forceinline__ void prolong_red_body(const Lv<T, 1> &F, const Lv<T, 
         const T ez0 = k > 0 ? blk(q - plane, i, j, k - 1) : blk(q, i ^ 1, j, k);
         const T ez1 = k < F.nz - 1 ? blk(q + plane, i, j, k + 1) : blk(q, i ^ 1, j, k);
         const T acc = rb_nb_sum(F, k, ex0, ex1, ey0, ey1, ez0, ez1);
-        er[q] = (rr + acc) / (F.dg[k] + (hs ? sg : T(0)));
+        er[q] = gs_value(rr + acc, F.dg[k] + (hs ? sg : T(0)));
     }
 }
 
@@ -1551,250 +1560,169 @@ __global__ __launch_bounds__(256) void k_prolong(const Inst<T> *I, Work w, int l
     else prolong_column<0>(F, C, X, m, j, t.tz * kProZ);
 }
 
-// --------------------------------------- temporal blocking below the finest level
-// On a red/black level small enough for its launches to be latency-bound, the
-// pre-smoothing sweeps and the restriction are one launch, and so are the
-// prolongation and the post-smoothing sweeps.  A block owns a tile of kTbT x kTbT
-// columns of every plane and keeps a box of the tile plus a kTbH-cell ring of
-// e in LDS, kTbQ threads per box column (each a share of its planes).  Each
-// half-sweep over the box leaves one ring fewer valid, so nu sweeps need a ring of
-// 2 nu cells (nu <= 2 here), recomputed by every block that needs it.  Every value
-// goes through the expressions of the separate launches (the zero-start value,
-// rb_nb_sum and the division by the same divisor; the lateral and z interpolants of
-// prolong_value; the restriction's residual and sums in the same order) with the same
-// operands, so the results are theirs bit for bit.
-//   pre:  nu zero-start sweeps on e (red then black), the restriction of the
-//         red children's residuals and of sigma into the coarse level, and the
-//         tile's black values stored in ealt (the only ones the post launch reads);
-//   post: black values of ealt plus the interpolated correction, nu sweeps (the
-//         first red half-sweep reads the corrected black values, as the fused
-//         prolongation does), and both colours of the tile stored in e.
-// The post launch reads ealt around its tile while other blocks store e, so the
-// two arrays keep the launches free of races.  Every global value a thread needs
-// (its cells' r and sigma, the coarse values it interpolates, its black values) is
-// loaded at the start in one round trip; the per-plane tables go to LDS, and the
-// sweeps then touch LDS alone.
-static_assert(kTbW * kTbW == 256, "a 256-column box");
+// ------------------------------------------------------------- temporal blocking
+// On a red/black level small enough for its launches to be latency-bound, the pre-smoothing
+// sweeps and the restriction are one launch, and so are the prolongation and the post-smoothing
+// sweeps.  A block owns a tile of kTbT x kTbT columns of every plane and keeps a box of the
+// tile plus a kTbH-cell ring of e in LDS.  Each half-sweep over the box leaves one ring
+// fewer valid, so nu sweeps need a ring of 2 nu cells (nu <= 2 here), recomputed by every block
+// that needs it.  Every value goes through the expressions of the launches it replaces (the
+// zero-start value, nb6, gs_value and res_value; the lateral and z interpolants of prolong_value;
+// the restriction's sums in order; the clipped Newton update) with the same operands, so the
+// results are theirs bit for bit.
+//   pre:  nu zero-start sweeps on e (red then black), the restriction of the red children's
+//         residuals and of sigma into the coarse level, and the tile's black values
+//         stored in ealt (the only ones the post launch reads);
+//   post: black values of ealt plus the interpolated correction, nu sweeps (the first red
+//         half-sweep reads the corrected black values, as the fused prolongation does),
+//         and both colours of the tile stored in e, or on the finest level phi_out =
+//         phi_in + clip(e) (nothing reads e there).
+// The post launch reads ealt around its tile while other blocks store e, so the two must not
+// overlap: ealt is an array of the level, the finer level's red half (dead between that
+// level's restriction and its next red half-sweep), or, on the finest level, e's own
+// black half (no e is stored there).
+//
+// What bounds it: four phases of LDS reads, each a chain of latencies (about 0.5 us), and the
+// LDS bandwidth of the box (4 times the tile's cells) on levels with many planes.  A wave
+// holds 64 box columns of one (x + y) parity, so the planes of its cells of one colour are the
+// same for all its lanes: the per-plane coefficients sit in scalar registers, the colours lie
+// in LDS arrays of their own (a column's cell and its x neighbours share or adjoin a pair), and
+// a wave's reads are contiguous.  Right-hand sides and reciprocal diagonals stay in registers
+// over all sweeps.  ZQ, the cells of one colour per thread, follows the level's planes.
+// Extents need not be multiples of the tile: the last tiles own what is left.
+constexpr int kTbThreads = kTbShares * kTbW * kTbW;
+constexpr int kTbPl = kTbW * kTbW / 2;        // box cells of one colour per plane
 constexpr int kTbCW = kTbW / 2 + 2;           // coarse columns under a box, with the interpolation's neighbours
-// Q threads per box column (256 Q per block), each with ZQ cells of one colour.
-template <int Q>
-struct TbShape {
-    static constexpr int threads = Q * kTbW * kTbW;
-    static constexpr int zq = (kTbMaxNz / 2 + Q - 1) / Q;
-};
-// Threads per column: four where the registers allow (FP32); in FP64 three for the
-// pre-smoothing and two for the post-smoothing, whose half-sweeps form two cells at a
-// time, so that neither spills registers.
-template <typename T> struct TbCfg {
-    static constexpr int pre_q = sizeof(T) == 8 ? 3 : 4, post_q = sizeof(T) == 8 ? 2 : 4;
-    static constexpr int post_g = sizeof(T) == 8 ? 2 : TbShape<post_q>::zq;
-};
+static_assert(kTbW == 16, "a wave's 64 lanes are 8 rows of 8 pairs");
 
 struct TbCol {
-    int gi, gj, ring, q0;                  // global column, its ring (0 inside the tile), pair index in a plane
+    int gi, gj, q0;                        // global column, its pair index in a plane
     int bx, by, tx, ty;                    // box column, tile
-    int z0;                                // first colour-cell index of this thread's share of the column
+    int ring;                              // 0 inside the tile
+    int li, xo;                            // LDS pair index in a plane; offset of the x neighbours' other pair
+    int par, z0, zf;                       // (x + y) parity, first cell index of the share, first one
+                                           // no earlier share has (uniform in a wave)
+    int np;                                // planes of one colour's array, two pads included
+    bool own;                              // column of the tile and of the grid
 };
 
 template <int ZQ, typename V>
 __device__ __forceinline__ TbCol tb_col(const V &L, int t) {
-    const int ntx = L.nx / kTbT;
+    const int ntx = (L.nx + kTbT - 1) / kTbT;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     TbCol c;
     c.ty = t / ntx;
     c.tx = t - c.ty * ntx;
-    c.bx = threadIdx.x & (kTbW - 1);
-    c.by = (threadIdx.x >> 4) & (kTbW - 1);
-    c.z0 = (threadIdx.x >> 8) * ZQ;       // threads 256 q .. 256 q + 255 take share q
+    c.par = wave & 1;
+    // shares of ZQ cells; the last ones move down so that none reaches past the top (cells of
+    // two shares get the same value twice)
+    const int nc = (L.nz + 1) / 2;
+    c.zf = (wave >> 2) * ZQ;
+    c.z0 = max(0, min(c.zf, nc - ZQ));
+    c.np = max(L.nz, 2 * ZQ) + 2;
+    c.by = (lane >> 3) + 8 * ((wave >> 1) & 1);
+    c.bx = 2 * (lane & 7) + ((c.by + c.par) & 1);
     int gi = c.tx * kTbT - kTbH + c.bx, gj = c.ty * kTbT - kTbH + c.by;
+    const int rx = c.bx < kTbH ? kTbH - c.bx : (c.bx >= kTbH + kTbT ? c.bx - (kTbH + kTbT - 1) : 0);
+    const int ry = c.by < kTbH ? kTbH - c.by : (c.by >= kTbH + kTbT ? c.by - (kTbH + kTbT - 1) : 0);
+    c.ring = rx > ry ? rx : ry;
+    c.own = c.ring == 0 && gi < L.nx && gj < L.ny;
     gi += gi < 0 ? L.nx : (gi >= L.nx ? -L.nx : 0);
     gj += gj < 0 ? L.ny : (gj >= L.ny ? -L.ny : 0);
     c.gi = gi;
     c.gj = gj;
-    const int rx = c.bx < kTbH ? kTbH - c.bx : (c.bx >= kTbH + kTbT ? c.bx - (kTbH + kTbT - 1) : 0);
-    const int ry = c.by < kTbH ? kTbH - c.by : (c.by >= kTbH + kTbT ? c.by - (kTbH + kTbT - 1) : 0);
-    c.ring = rx > ry ? rx : ry;
     c.q0 = gj * (L.nx >> 1) + (gi >> 1);
+    c.li = c.by * (kTbW / 2) + (c.bx >> 1);
+    c.xo = (c.bx & 1) ? 1 : -1;
     return c;
 }
 
-// Plane of this thread's z-th cell of colour col (planes past the top are clamped: their
-// values are formed but never stored).
-__device__ __forceinline__ int tb_k(const TbCol &c, int col, int z, int nz) {
-    return min(2 * (c.z0 + z) + ((col + c.bx + c.by) & 1), nz - 1);
-}
-__device__ __forceinline__ bool tb_in(const TbCol &c, int col, int z, int nz) {
-    return 2 * (c.z0 + z) + ((col + c.bx + c.by) & 1) < nz;
-}
-__device__ __forceinline__ int tb_l(const TbCol &c, int k) { return (k * kTbW + c.by) * kTbW + c.bx; }
-
-// LDS after the box: the level's per-plane tables (cxy, czm, czp, dg), the z weights
-// and parent planes of its prolongation (pwa, pwb, pka, pkb).
+// Colour col's array of the box (the caller's column added): plane k at k kTbPl.  The planes
+// below the lowest and above the highest cell are pads of zeros, so that every cell reads both
+// z neighbours (with weight 0 at the contacts) at fixed offsets.
 template <typename T>
-struct TbTab {
-    Lv<T, 3> L;                            // the level with its tables in LDS (no arrays)
-    const T FX_AS(3) *pwa, *pwb;
-    const int FX_AS(3) *pka, *pkb;
+__device__ __forceinline__ T FX_AS(3) *tb_array(T FX_AS(3) *box, const TbCol &c, int col) {
+    return box + (col * c.np + 1) * kTbPl + c.li;
+}
+template <typename T>
+__device__ __forceinline__ void tb_pads(T FX_AS(3) *box, const TbCol &c, int nz) {
+    const int t = threadIdx.x;
+    if (t < 4 * kTbPl) box[((t >> 8) * c.np + ((t >> 7) & 1) * (nz + 1)) * kTbPl + (t & (kTbPl - 1))] = T(0);
+}
+
+// Plane of this thread's z-th cell of colour col (past the top on levels with few planes or an
+// odd count: such cells are formed from whatever lies there and never stored).
+__device__ __forceinline__ int tb_k(const TbCol &c, int col, int z) { return 2 * (c.z0 + z) + ((col + c.par) & 1); }
+
+// This thread's cells of both colours: right-hand sides and reciprocal diagonals (vectors),
+// coefficients (scalars).
+template <typename T, int ZQ>
+struct TbCells {
+    T r[2][ZQ], iv[2][ZQ], cx[2][ZQ], cm[2][ZQ], cp[2][ZQ];
+
+    // idg: room for the reciprocal diagonals of the planes without sigma, formed once per block
+    // (a division per cell cost 3 us a launch); its barrier also publishes the caller's stores.
+    __device__ __forceinline__ void load(const Lv<T, 1> &L, const TbCol &c, T FX_AS(3) *idg) {
+        const int plane = L.ny * (L.nx >> 1), half = plane * L.nz, hsz = plane * (L.sig_hi - L.sig_lo);
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int z = 0; z < ZQ; ++z) {
+                const int k = min(tb_k(c, col, z), L.nz - 1);
+                r[col][z] = L.r[col * half + k * plane + c.q0];
+                iv[col][z] = T(0);
+                if (has_sig(L, k)) iv[col][z] = L.sig[col * hsz + (k - L.sig_lo) * plane + c.q0];
+            }
+        for (int k = threadIdx.x; k < L.nz; k += kTbThreads) idg[k] = T(1) / L.dg[k];
+        __syncthreads();
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int z = 0; z < ZQ; ++z) {
+                const int k = min(tb_k(c, col, z), L.nz - 1);
+                cx[col][z] = L.cxy[k];
+                cm[col][z] = k > 0 ? L.czm[k] : T(0);
+                cp[col][z] = k < L.nz - 1 ? L.czp[k] : T(0);
+                if (has_sig(L, k)) iv[col][z] = T(1) / (L.dg[k] + iv[col][z]);
+                else iv[col][z] = idg[k];
+            }
+    }
+    // neighbour sum of colour col's z-th cell; eo: the other colour's array
+    __device__ __forceinline__ T nb(const TbCol &c, const T FX_AS(3) *eo, int col, int z) const {
+        const T FX_AS(3) *e = eo + (2 * c.z0 + ((col + c.par) & 1)) * kTbPl + 2 * z * kTbPl;
+        return nb6(cx[col][z], cx[col][z], cm[col][z], cp[col][z], e[0], e[c.xo], e[kTbW / 2], e[-(kTbW / 2)], e[-kTbPl],
+                   e[kTbPl]);
+    }
+    // One half-sweep of colour col over the box columns within ring R (ZI: from a zero
+    // start).  Cells of one colour are not neighbours, so the new values of a group of cells
+    // are formed before any of them is stored (the group bounds the registers held).
+    template <int ZI>
+    __device__ __forceinline__ void half_sweep(const TbCol &c, int nz, T FX_AS(3) *box, int col, int R) const {
+        constexpr int G = ZQ <= 4 ? ZQ : ZQ / 2;
+        T FX_AS(3) *es = tb_array(box, c, col);
+        const T FX_AS(3) *eo = tb_array(box, c, 1 - col);
+        if (c.ring <= R) {
+#pragma unroll
+            for (int z0 = 0; z0 < ZQ; z0 += G) {
+                T v[G];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int z = z0 + g;
+                    v[g] = (ZI ? r[col][z] : r[col][z] + nb(c, eo, col, z)) * iv[col][z];
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int k = tb_k(c, col, z0 + g);
+                    if (k < nz) es[k * kTbPl] = v[g];
+                }
+            }
+        }
+        __syncthreads();
+    }
 };
 
-template <typename T>
-__device__ __forceinline__ TbTab<T> tb_tables(const Lv<T, 1> &L, const Xv<T> &X, T FX_AS(3) *box, int with_z) {
-    T FX_AS(3) *tab = box + L.nz * kTbW * kTbW;
-    int FX_AS(3) *itab = (int FX_AS(3) *)(tab + 6 * L.nz);
-    for (int c = threadIdx.x; c < L.nz; c += blockDim.x) {
-        tab[c] = L.cxy[c];
-        tab[L.nz + c] = L.czm[c];
-        tab[2 * L.nz + c] = L.czp[c];
-        tab[3 * L.nz + c] = L.dg[c];
-        if (with_z) {
-            tab[4 * L.nz + c] = X.pwa[c];
-            tab[5 * L.nz + c] = X.pwb[c];
-            itab[c] = X.pka[c];
-            itab[L.nz + c] = X.pkb[c];
-        }
-    }
-    TbTab<T> t;
-    t.L.nx = L.nx; t.L.ny = L.ny; t.L.nz = L.nz; t.L.rb = L.rb;
-    t.L.cxy = tab; t.L.czm = tab + L.nz; t.L.czp = tab + 2 * L.nz; t.L.dg = tab + 3 * L.nz;
-    t.L.e = nullptr; t.L.r = nullptr; t.L.sig = nullptr;
-    t.L.sig_lo = L.sig_lo; t.L.sig_hi = L.sig_hi;
-    t.pwa = tab + 4 * L.nz; t.pwb = tab + 5 * L.nz;
-    t.pka = itab; t.pkb = itab + L.nz;
-    return t;
-}
-
-// This thread's cells of colour col: right-hand sides and sigma (0 off the
-// semiconductor planes), loaded without conditions.
 template <typename T, int ZQ>
-__device__ __forceinline__ void tb_col_rs(const Lv<T, 1> &L, const TbCol &c, int col, T (&rr)[ZQ], T (&sg)[ZQ]) {
-    const int plane = L.ny * (L.nx >> 1);
-    const int half = plane * L.nz;
-    const int hsz = plane * (L.sig_hi - L.sig_lo);
-    const T FX_AS(1) *rs = L.r + (col ? half : 0);
-    const T FX_AS(1) *ss = L.sig + (col ? hsz : 0);
-#pragma unroll
-    for (int z = 0; z < ZQ; ++z) {
-        const int k = tb_k(c, col, z, L.nz);
-        const bool hs = k >= L.sig_lo && k < L.sig_hi;
-        rr[z] = rs[k * plane + c.q0];
-        const T v = ss[hs ? (k - L.sig_lo) * plane + c.q0 : 0];
-        sg[z] = hs ? v : T(0);
-    }
-}
-// The divisors, as the separate half-sweeps form them (tables in LDS hold the same values).
-template <typename T, int ZQ>
-__device__ __forceinline__ void tb_col_den(const Lv<T, 3> &Lt, const TbCol &c, int col, T (&sg)[ZQ]) {
-#pragma unroll
-    for (int z = 0; z < ZQ; ++z) {
-        const int k = tb_k(c, col, z, Lt.nz);
-        const bool hs = k >= Lt.sig_lo && k < Lt.sig_hi;
-        sg[z] = Lt.dg[k] + (hs ? sg[z] : T(0));
-    }
-}
-
-// One half-sweep of colour col over the box columns within ring R (ZI: from a zero
-// start).  The box origin is even in x and y, so a box cell's colour is the parity of
-// its box coordinates and plane, and its red/black partner (the other cell of its
-// storage pair, the stand-in operand of the zero-coefficient z terms) is box x ^ 1.
-// Cells of one colour are not neighbours, so the new values of a group of G cells are
-// formed before any of them is stored (G bounds the registers held by the operands).
-template <typename T, int ZI, int ZQ, int G = ZQ>
-__device__ __forceinline__ void tb_half(const Lv<T, 3> &Lt, const TbCol &c, T FX_AS(3) *box, int col, int R,
-                                        const T (&rr)[ZQ], const T (&den)[ZQ]) {
-    if (c.ring <= R) {
-#pragma unroll
-        for (int z0 = 0; z0 < ZQ; z0 += G) {
-            T v[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int z = z0 + g < ZQ ? z0 + g : ZQ - 1;
-                const int k = tb_k(c, col, z, Lt.nz);
-                const int l = tb_l(c, k);
-                T acc = 0;
-                if (!ZI) {
-                    const T ez0 = k > 0 ? box[l - kTbW * kTbW] : box[l ^ 1];
-                    const T ez1 = k < Lt.nz - 1 ? box[l + kTbW * kTbW] : box[l ^ 1];
-                    acc = rb_nb_sum(Lt, k, box[l + 1], box[l - 1], box[l + kTbW], box[l - kTbW], ez0, ez1);
-                }
-                v[g] = (rr[z] + acc) / den[z];
-            }
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (z0 + g < ZQ && tb_in(c, col, z0 + g, Lt.nz)) box[tb_l(c, tb_k(c, col, z0 + g, Lt.nz))] = v[g];
-        }
-    }
-    __syncthreads();
-}
-
-// Restriction of coarse cell (I, J, K) from the box (restrict_cell_rbxy's loads and
-// arithmetic; the box holds e, the tile's red cells and their black neighbours valid).
-template <typename T, typename X>
-__device__ __forceinline__ void tb_restrict_cell(const Lv<T, 1> &F, const Lv<T, 1> &C, const X &Xf, const T FX_AS(3) *box,
-                                                 int I, int J, int K, int bx0, int by0) {
-    const int ks = Xf.cks[K], cnt = Xf.ccnt[K];
-    T sg[2][2][2], rv[2][2], ev[2][2], nb[2][2][6], cx[2], czm[2], czp[2], dg[2];
-#pragma unroll
-    for (int dz = 0; dz < 2; ++dz) {
-        const int k = ks + (dz < cnt ? dz : 0);
-        const bool hs = has_sig(F, k);
-        const int km = k > 0 ? k - 1 : k, kp = k < F.nz - 1 ? k + 1 : k;
-        cx[dz] = F.cxy[k];
-        czm[dz] = F.czm[k];
-        czp[dz] = F.czp[k];
-        dg[dz] = F.dg[k];
-#pragma unroll
-        for (int dy = 0; dy < 2; ++dy) {
-            const int j = 2 * J + dy;
-#pragma unroll
-            for (int dx = 0; dx < 2; ++dx) {
-                const int i = 2 * I + dx;
-                const T FX_AS(1) *sp = hs ? F.sig + sidx(F, i, j, k) : F.r + cidx(F, i, j, k);
-                sg[dz][dy][dx] = *sp;
-            }
-            const int dxr = (dy + k) & 1;
-            const int i = 2 * I + dxr;
-            rv[dz][dy] = F.r[cidx(F, i, j, k)];
-            const int l = (k * kTbW + by0 + dy) * kTbW + bx0 + dxr;
-            ev[dz][dy] = box[l];
-            nb[dz][dy][0] = box[l + 1];
-            nb[dz][dy][1] = box[l - 1];
-            nb[dz][dy][2] = box[l + kTbW];
-            nb[dz][dy][3] = box[l - kTbW];
-            nb[dz][dy][4] = box[l + (km - k) * kTbW * kTbW];
-            nb[dz][dy][5] = box[l + (kp - k) * kTbW * kTbW];
-        }
-    }
-    double sr = 0.0, ss = 0.0;
-#pragma unroll
-    for (int dz = 0; dz < 2; ++dz) {
-        if (dz >= cnt) break;
-        const int k = ks + dz;
-        const double wz = (double)Xf.fthick[k] / (double)Xf.cthick[K];
-        const bool hs = has_sig(F, k);
-#pragma unroll
-        for (int dy = 0; dy < 2; ++dy) {
-#pragma unroll
-            for (int dx = 0; dx < 2; ++dx) {
-                const T sgc = hs ? sg[dz][dy][dx] : T(0);
-                ss += wz * (double)sgc;
-                if (dx != ((dy + k) & 1)) continue;
-                T nbs = 0;
-                nbs += cx[dz] * (nb[dz][dy][0] + nb[dz][dy][1]);
-                nbs += cx[dz] * (nb[dz][dy][2] + nb[dz][dy][3]);
-                if (k > 0) nbs += czm[dz] * nb[dz][dy][4];
-                if (k < F.nz - 1) nbs += czp[dz] * nb[dz][dy][5];
-                const T res = rv[dz][dy] - ((dg[dz] + sgc) * ev[dz][dy] - nbs);
-                sr += wz * (double)res;
-            }
-        }
-    }
-    C.r[cidx(C, I, J, K)] = (T)(sr * 0.25);
-    if (has_sig(C, K)) C.sig[sidx(C, I, J, K)] = (T)(ss * 0.25);
-}
-
-template <typename T>
-__global__ __launch_bounds__(TbShape<TbCfg<T>::pre_q>::threads) void k_pre_tb(const Inst<T> *I, Work w, int level,
-                                                                                int nu) {
-    constexpr int ZQ = TbShape<TbCfg<T>::pre_q>::zq;
+__global__ __launch_bounds__(kTbThreads) void k_pre_tb(const Inst<T> *I, Work w, int level, int nu) {
     extern __shared__ double tb_raw[];
     const Blk b = find_block(w);
     const Inst<T> &a = I[b.inst];
@@ -1804,46 +1732,75 @@ __global__ __launch_bounds__(TbShape<TbCfg<T>::pre_q>::threads) void k_pre_tb(co
     if (light) nu = 1;                         // the sweeps after the first are left out
     const Lv<T, 1> L = gview(a.lv[level]);
     const Xv<T> X = xview(a.xf[level]);
+    const Lv<T, 1> C = gview(a.lv[level + 1]);
     T FX_AS(3) *box = asp<3>((T *)tb_raw);
     const TbCol c = tb_col<ZQ>(L, b.t);
-    T rr0[ZQ], den0[ZQ], rr1[ZQ], den1[ZQ];
-    tb_col_rs(L, c, 0, rr0, den0);
-    tb_col_rs(L, c, 1, rr1, den1);
-    const TbTab<T> tt = tb_tables(L, X, box, 0);
-    __syncthreads();                               // tables
-    tb_col_den(tt.L, c, 0, den0);
-    tb_col_den(tt.L, c, 1, den1);
-    tb_half<T, 1>(tt.L, c, box, 0, 2 * nu, rr0, den0);
-    tb_half<T, 0>(tt.L, c, box, 1, 2 * nu - 1, rr1, den1);
-    if (nu > 1) {
-        tb_half<T, 0>(tt.L, c, box, 0, 2, rr0, den0);
-        tb_half<T, 0>(tt.L, c, box, 1, 1, rr1, den1);
+    const int nz = L.nz;
+    tb_pads(box, c, nz);
+    TbCells<T, ZQ> m;
+    m.load(L, c, box + 2 * c.np * kTbPl);
+    // sigma of the tile's coarse cells (kTbT/2 x kTbT/2 columns of every coarse plane)
+    constexpr int kC = kTbT / 2;
+    for (int u = threadIdx.x; u < kC * kC * (C.sig_hi - C.sig_lo); u += kTbThreads) {
+        const int K = C.sig_lo + u / (kC * kC), J = c.ty * kC + u / kC % kC, I0 = c.tx * kC + u % kC;
+        if (I0 >= C.nx || J >= C.ny) continue;
+        const int ks = X.cks[K], cnt = X.ccnt[K];
+        double ss = 0.0;
+        for (int dz = 0; dz < cnt; ++dz) {
+            const double wz = (double)X.fthick[ks + dz] / (double)X.cthick[K];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const T sg = has_sig(L, ks + dz) ? L.sig[sidx(L, 2 * I0 + (q & 1), 2 * J + (q >> 1), ks + dz)] : T(0);
+                ss = fmad(wz, (double)sg, ss);
+            }
+        }
+        C.sig[sidx(C, I0, J, K)] = (T)(ss * 0.25);
     }
-    // the tile's black values for the post launch
-    if (c.ring == 0) {
-        const int plane = L.ny * (L.nx >> 1), half = plane * L.nz;
+    m.template half_sweep<1>(c, nz, box, 0, 2 * nu);
+    m.template half_sweep<0>(c, nz, box, 1, 2 * nu - 1);
+    if (nu > 1) {
+        m.template half_sweep<0>(c, nz, box, 0, 2);
+        m.template half_sweep<0>(c, nz, box, 1, 1);
+    }
+    T FX_AS(3) *red = tb_array(box, c, 0);
+    const T FX_AS(3) *blk = tb_array(box, c, 1);
+    const int plane = L.ny * (L.nx >> 1);
+    if (c.own) {
+        // the tile's black values for the post launch; its red residuals into the red cells
         T FX_AS(1) *ealt = asp<1>(a.lv[level].ealt);
 #pragma unroll
         for (int z = 0; z < ZQ; ++z) {
-            const int k = tb_k(c, 1, z, L.nz);
-            if (tb_in(c, 1, z, L.nz)) ealt[half + k * plane + c.q0] = box[tb_l(c, k)];
+            const int k = tb_k(c, 1, z);
+            if (k < nz) ealt[k * plane + c.q0] = blk[k * kTbPl];
+        }
+#pragma unroll
+        for (int z = 0; z < ZQ; ++z) {
+            const int k = tb_k(c, 0, z);
+            if (k >= nz || c.z0 + z < c.zf) continue;
+            T d = L.dg[k];
+            if (has_sig(L, k)) d += L.sig[(k - L.sig_lo) * plane + c.q0];
+            red[k * kTbPl] = res_value(m.r[0][z], d, red[k * kTbPl], m.nb(c, blk, 0, z));
         }
     }
-    // restriction: kTbT/2 x kTbT/2 coarse columns of the tile, every coarse plane
-    const Lv<T, 1> C = gview(a.lv[level + 1]);
-    constexpr int kC = kTbT / 2;
-    for (int u = threadIdx.x; u < kC * kC * C.nz; u += blockDim.x) {
-        const int K = u / (kC * kC), cc = u - K * kC * kC;
-        const int cj = cc / kC, ci = cc - cj * kC;
-        tb_restrict_cell(L, C, X, box, c.tx * kC + ci, c.ty * kC + cj, K, kTbH + 2 * ci, kTbH + 2 * cj);
+    __syncthreads();
+    for (int u = threadIdx.x; u < kC * kC * C.nz; u += kTbThreads) {
+        const int K = u / (kC * kC), cj = u / kC % kC, ci = u % kC;
+        const int J = c.ty * kC + cj, I0 = c.tx * kC + ci;
+        if (I0 >= C.nx || J >= C.ny) continue;
+        const int ks = X.cks[K], cnt = X.ccnt[K];
+        double sr = 0.0;
+        for (int dz = 0; dz < cnt; ++dz) {
+            const double wz = (double)X.fthick[ks + dz] / (double)X.cthick[K];
+            const T FX_AS(3) *p = box + (ks + dz + 1) * kTbPl + (kTbH + 2 * cj) * (kTbW / 2) + kTbH / 2 + ci;
+            sr = fmad(wz, (double)p[0], sr);
+            sr = fmad(wz, (double)p[kTbW / 2], sr);
+        }
+        C.r[cidx(C, I0, J, K)] = (T)(sr * 0.25);
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(TbShape<TbCfg<T>::post_q>::threads) void k_post_tb(const Inst<T> *I, Work w, int level,
-                                                                                  int nu) {
-    constexpr int ZQ = TbShape<TbCfg<T>::post_q>::zq;
-    constexpr int G = TbCfg<T>::post_g;
+template <typename T, int ZQ, int FINEST>
+__global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w, int level, int nu) {
     extern __shared__ double tb_raw[];
     const Blk b = find_block(w);
     const Inst<T> &a = I[b.inst];
@@ -1856,32 +1813,33 @@ __global__ __launch_bounds__(TbShape<TbCfg<T>::post_q>::threads) void k_post_tb(
     const Xv<T> X = xview(a.xf[level]);
     T FX_AS(3) *box = asp<3>((T *)tb_raw);
     const TbCol c = tb_col<ZQ>(F, b.t);
-    const int plane = F.ny * (F.nx >> 1), half = plane * F.nz;
-    const bool corr = c.ring <= 2 * nu;
-    // The coarse values under the box (kTbCW x kTbCW coarse columns, every coarse plane),
-    // one load each, into the box's planes above those the interpolants take; then this
-    // thread's black values.  Box column bx lies over coarse box column
-    // (tile x - kTbH + bx) / 2 - (tile x kTbT/2 - kTbH/2 - 1), its x neighbour one further
-    // on the side of its parity, as prolong_value takes them (wrapping included).
-    T FX_AS(3) *cb = box + C.nz * kTbW * kTbW;
+    const int nz = F.nz;
+    const int plane = F.ny * (F.nx >> 1), half = plane * nz;
+    // The coarse values under the box (kTbCW x kTbCW coarse columns, every coarse plane), one
+    // load each, above the box in LDS; then this thread's cells.  Box column bx lies over coarse
+    // box column (tile x - kTbH + bx) / 2 - (tile x kTbT/2 - kTbH/2 - 1), its x neighbour one
+    // further on the side of its parity, as prolong_value takes them (wrapping included).
+    T FX_AS(3) *cb = box + 2 * c.np * kTbPl;
     const int cx0 = c.tx * (kTbT / 2) - kTbH / 2 - 1, cy0 = c.ty * (kTbT / 2) - kTbH / 2 - 1;
-    for (int u = threadIdx.x; u < kTbCW * kTbCW * C.nz; u += blockDim.x) {
+    for (int u = threadIdx.x; u < kTbCW * kTbCW * C.nz; u += kTbThreads) {
         const int K = u / (kTbCW * kTbCW), rem = u - K * kTbCW * kTbCW;
         const int cj = rem / kTbCW, ci = rem - cj * kTbCW;
-        int I = cx0 + ci, J = cy0 + cj;
-        I += I < 0 ? C.nx : (I >= C.nx ? -C.nx : 0);
+        int I0 = cx0 + ci, J = cy0 + cj;
+        I0 += I0 < 0 ? C.nx : (I0 >= C.nx ? -C.nx : 0);
         J += J < 0 ? C.ny : (J >= C.ny ? -C.ny : 0);
-        cb[u] = C.e[cidx(C, I, J, K)];
+        cb[u] = C.e[cidx(C, I0, J, K)];
     }
-    T ebv[ZQ];
-    const T FX_AS(1) *eb = asp<1>(a.lv[level].ealt) + half;
+    T eb[ZQ];
+    const T FX_AS(1) *ea = asp<1>(a.lv[level].ealt);
 #pragma unroll
-    for (int z = 0; z < ZQ; ++z) ebv[z] = eb[tb_k(c, 1, z, F.nz) * plane + c.q0];
-    const TbTab<T> tt = tb_tables(F, X, box, 1);
-    __syncthreads();                               // coarse values, tables
-    // the lateral interpolants (prolong_value's weights and operands), parked in the box
-    // for the z interpolation
-    if (corr) {
+    for (int z = 0; z < ZQ; ++z) eb[z] = ea[min(tb_k(c, 1, z), nz - 1) * plane + c.q0];
+    tb_pads(box, c, nz);
+    TbCells<T, ZQ> m;
+    m.load(F, c, cb + kTbCW * kTbCW * C.nz);
+    T FX_AS(3) *blk = tb_array(box, c, 1);
+    if (c.ring <= 2 * nu) {
+        // the correction of the black cells: lint_z of the lateral interpolants on the parent
+        // and neighbour planes (prolong_value's weights and operands)
         const T wx[2] = {T(0.75), T(0.25)}, wy[2] = {T(0.75), T(0.25)};
         T wgt[2][2];
 #pragma unroll
@@ -1889,62 +1847,68 @@ __global__ __launch_bounds__(TbShape<TbCfg<T>::post_q>::threads) void k_post_tb(
 #pragma unroll
             for (int xx = 0; xx < 2; ++xx) wgt[yy][xx] = wx[xx] * wy[yy];
         const int gu = c.tx * kTbT - kTbH + c.bx, gv = c.ty * kTbT - kTbH + c.by;   // unwrapped
-        const int ci[2] = {(gu >> 1) - cx0, (gu >> 1) - cx0 + ((gu & 1) ? 1 : -1)};
-        const int cj[2] = {(gv >> 1) - cy0, (gv >> 1) - cy0 + ((gv & 1) ? 1 : -1)};
-        T sv[ZQ];
-#pragma unroll
-        for (int q = 0; q < ZQ; ++q) {
-            const int K = min(c.z0 + q, C.nz - 1);
-            T v[2][2];
-#pragma unroll
-            for (int yy = 0; yy < 2; ++yy)
-#pragma unroll
-                for (int xx = 0; xx < 2; ++xx) v[yy][xx] = cb[(K * kTbCW + cj[yy]) * kTbCW + ci[xx]];
-            sv[q] = lint_xy<2, 2>(wgt, v);
-        }
-#pragma unroll
-        for (int q = 0; q < ZQ; ++q)
-            if (c.z0 + q < C.nz) box[tb_l(c, c.z0 + q)] = sv[q];
-    }
-    __syncthreads();                               // interpolants
-    // black values with the correction: eb + lint_z of the parent and neighbour planes
-    T vb[ZQ];
-    if (corr) {
+        const int ci = (gu >> 1) - cx0, cj = (gv >> 1) - cy0;
+        const int o[2][2] = {{cj * kTbCW + ci, cj * kTbCW + ci + ((gu & 1) ? 1 : -1)},
+                             {(cj + ((gv & 1) ? 1 : -1)) * kTbCW + ci,
+                              (cj + ((gv & 1) ? 1 : -1)) * kTbCW + ci + ((gu & 1) ? 1 : -1)}};
 #pragma unroll
         for (int z = 0; z < ZQ; ++z) {
-            const int k = tb_k(c, 1, z, F.nz);
-            const int ka = tt.pka[k], kb = tt.pkb[k];
-            const T s0 = box[tb_l(c, ka)];
-            const T s1 = box[tb_l(c, kb >= 0 ? kb : ka)];
-            vb[z] = ebv[z] + lint_z(tt.pwa[k], s0, kb >= 0 ? tt.pwb[k] : T(0), s1);
+            const int kk = tb_k(c, 1, z), k = min(kk, nz - 1);
+            const int ka = X.pka[k], kb = X.pkb[k];
+            T sp[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const T FX_AS(3) *p = cb + (q == 0 || kb < 0 ? ka : kb) * (kTbCW * kTbCW);
+                T v[2][2];
+#pragma unroll
+                for (int yy = 0; yy < 2; ++yy)
+#pragma unroll
+                    for (int xx = 0; xx < 2; ++xx) v[yy][xx] = p[o[yy][xx]];
+                sp[q] = lint_xy<2, 2>(wgt, v);
+            }
+            const T v = eb[z] + lint_z(T(X.pwa[k]), sp[0], kb >= 0 ? T(X.pwb[k]) : T(0), sp[1]);
+            if (kk < nz) blk[k * kTbPl] = v;
         }
     }
-    __syncthreads();                               // interpolants read
-    if (corr) {
-#pragma unroll
-        for (int z = 0; z < ZQ; ++z)
-            if (tb_in(c, 1, z, F.nz)) box[tb_l(c, tb_k(c, 1, z, F.nz))] = vb[z];
-    }
-    // this thread's cells' r and sigma (loaded after the correction, which needs the registers)
-    T rr0[ZQ], den0[ZQ], rr1[ZQ], den1[ZQ];
-    tb_col_rs(F, c, 0, rr0, den0);
-    tb_col_rs(F, c, 1, rr1, den1);
-    tb_col_den(tt.L, c, 0, den0);
-    tb_col_den(tt.L, c, 1, den1);
     __syncthreads();
-    tb_half<T, 0, ZQ, G>(tt.L, c, box, 0, 2 * nu - 1, rr0, den0);
-    tb_half<T, 0, ZQ, G>(tt.L, c, box, 1, 2 * nu - 2, rr1, den1);
+    m.template half_sweep<0>(c, nz, box, 0, 2 * nu - 1);
+    m.template half_sweep<0>(c, nz, box, 1, 2 * nu - 2);
     if (nu > 1) {
-        tb_half<T, 0, ZQ, G>(tt.L, c, box, 0, 1, rr0, den0);
-        tb_half<T, 0, ZQ, G>(tt.L, c, box, 1, 0, rr1, den1);
+        m.template half_sweep<0>(c, nz, box, 0, 1);
+        m.template half_sweep<0>(c, nz, box, 1, 0);
     }
-    if (c.ring == 0) {
+    if (!c.own) return;
+    if (FINEST) {
+        const size_t off = (size_t)a.kb * a.nx * a.ny;
+        const double FX_AS(1) *phi_in = asp<1>(a.phi[cyc_src(st)]) + off;
+        double FX_AS(1) *phi_out = asp<1>(a.phi[cyc_dst(st)]) + off;
+        const int FX_AS(1) *pflags = asp<1>(a.pflags);
+        const int col0 = c.gj * F.nx + c.gi, nxy = F.nx * F.ny;
+        double ph[2][ZQ], lim[2][ZQ];
 #pragma unroll
         for (int col = 0; col < 2; ++col)
 #pragma unroll
             for (int z = 0; z < ZQ; ++z) {
-                const int k = tb_k(c, col, z, F.nz);
-                if (tb_in(c, col, z, F.nz)) F.e[(col ? half : 0) + k * plane + c.q0] = box[tb_l(c, k)];
+                const int k = min(tb_k(c, col, z), nz - 1);
+                ph[col][z] = phi_in[(size_t)k * nxy + col0];
+                lim[col][z] = (pflags[k] & PF_SC) ? a.dmax : 1e300;
+            }
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int z = 0; z < ZQ; ++z) {
+                const int k = tb_k(c, col, z);
+                if (k >= nz) continue;
+                const double d = (double)tb_array(box, c, col)[k * kTbPl];
+                phi_out[(size_t)k * nxy + col0] = ph[col][z] + fmin(fmax(d, -lim[col][z]), lim[col][z]);
+            }
+    } else {
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int z = 0; z < ZQ; ++z) {
+                const int k = tb_k(c, col, z);
+                if (k < nz) F.e[col * half + k * plane + c.q0] = tb_array(box, c, col)[k * kTbPl];
             }
     }
 }
@@ -2025,8 +1989,7 @@ struct RbCells {
     // neighbour sum of colour c2's cell of pair p
     __device__ __forceinline__ T nb(const T FX_AS(3) *eo, int c2, int p) const {
         const T FX_AS(3) *e = eo + q[p];
-        const T x = e[0] + e[dx[c2][p]], y = e[oy[0][p]] + e[oy[1][p]];
-        return fmad(cp[p], e[oz[1][p]], fmad(cm[p], e[oz[0][p]], fmad(cy[p], y, cx[p] * x)));
+        return nb6(cx[p], cy[p], cm[p], cp[p], e[0], e[dx[c2][p]], e[oy[0][p]], e[oy[1][p]], e[oz[0][p]], e[oz[1][p]]);
     }
     __device__ __forceinline__ void half_sweep(const Lv<T, 3> &L, int c2, int zero_init) const {
         const int n = (L.nx >> 1) * L.ny * L.nz;
@@ -2050,7 +2013,7 @@ struct RbCells {
             const int k = fquo(fquo(q[p], sp.fx), sp.fy);
             T d = L.dg[k];
             if (k >= L.sig_lo && k < L.sig_hi) d += L.sig[q[p] - L.sig_lo * plane];
-            v[p] = r[0][p] - fmad(d, L.e[q[p]], -nb(L.e + n, 0, p));
+            v[p] = res_value(r[0][p], d, L.e[q[p]], nb(L.e + n, 0, p));
         }
 #pragma unroll
         for (int p = 0; p < NP; ++p)
@@ -2734,16 +2697,37 @@ void launch_prolong_cc(const Inst<T> *I, const Work &w, int level, int cz, hipSt
 }
 
 template <typename T>
-void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int lds_bytes, hipStream_t st) {
+void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, hipStream_t st) {
     if (w.total <= 0) return;
-    hipLaunchKernelGGL(k_pre_tb<T>, grid_of(w.total), dim3(TbShape<TbCfg<T>::pre_q>::threads), lds_bytes, st, I, w,
-                       level, nu);
+    const size_t lds = tb_lds_bytes(nz, 0, sizeof(T));
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid_of(w.total), dim3(kTbThreads), lds, st, I, w, level, nu); };
+    switch (tb_zq(nz)) {
+        case 1: go(k_pre_tb<T, 1>); break;
+        case 2: go(k_pre_tb<T, 2>); break;
+        case 3: go(k_pre_tb<T, 3>); break;
+        case 4: go(k_pre_tb<T, 4>); break;
+        case 6: go(k_pre_tb<T, 6>); break;
+        default: go(k_pre_tb<T, 8>); break;
+    }
+}
+template <typename T, int FINEST>
+static void launch_post_tb_f(const Inst<T> *I, const Work &w, int level, int nu, int nz, int nzc, hipStream_t st) {
+    const size_t lds = tb_lds_bytes(nz, nzc, sizeof(T));
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid_of(w.total), dim3(kTbThreads), lds, st, I, w, level, nu); };
+    switch (tb_zq(nz)) {
+        case 1: go(k_post_tb<T, 1, FINEST>); break;
+        case 2: go(k_post_tb<T, 2, FINEST>); break;
+        case 3: go(k_post_tb<T, 3, FINEST>); break;
+        case 4: go(k_post_tb<T, 4, FINEST>); break;
+        case 6: go(k_post_tb<T, 6, FINEST>); break;
+        default: go(k_post_tb<T, 8, FINEST>); break;
+    }
 }
 template <typename T>
-void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int lds_bytes, hipStream_t st) {
+void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, int nzc, hipStream_t st) {
     if (w.total <= 0) return;
-    hipLaunchKernelGGL(k_post_tb<T>, grid_of(w.total), dim3(TbShape<TbCfg<T>::post_q>::threads), lds_bytes, st, I, w,
-                       level, nu);
+    if (level == 0) launch_post_tb_f<T, 1>(I, w, level, nu, nz, nzc, st);
+    else launch_post_tb_f<T, 0>(I, w, level, nu, nz, nzc, st);
 }
 template <typename T>
 void launch_coarse(const Inst<T> *I, InstState *S, int ninst, int lds_bytes, hipStream_t st) {
@@ -2796,8 +2780,8 @@ void launch_fill(double *x, size_t n, double v, hipStream_t st) {
     template void launch_prolong<T>(const Inst<T> *, const Work &, int, hipStream_t);                        \
     template void launch_prolong_cc<T>(const Inst<T> *, const Work &, int, int, hipStream_t);                \
     template void launch_coarse<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                      \
-    template void launch_pre_tb<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);                 \
-    template void launch_post_tb<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);                                  \
+    template void launch_pre_tb<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);                \
+    template void launch_post_tb<T>(const Inst<T> *, const Work &, int, int, int, int, hipStream_t);          \
     template void launch_head<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                                    \
     template void launch_run_setup<T>(const Inst<T> *, int, int, int, double, int, hipStream_t);             \
     template void launch_set_vtop<T>(const Inst<T> *, int, double, hipStream_t);

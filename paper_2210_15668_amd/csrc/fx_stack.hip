@@ -343,7 +343,7 @@ struct Engine {
     ResWork w_res{};
     std::vector<Work> w_sm, w_rs, w_pr, w_prc;   // w_pr / w_prc: prolongation by fine or by coarse columns
     std::vector<Work> w_tb;             // blocked smoothing: a block per tile
-    std::vector<int> tb, tb_lds;        // level smoothed in blocks; LDS bytes of its box
+    std::vector<int> tb, tb_nz, tb_nzc; // level smoothed in blocks; the most planes on it and on the next
     std::vector<int> prc_cz;            // coarse planes per thread of w_prc, per level
     std::vector<SmoothCfg> scfg;        // smoother launch shape per level
     std::vector<int> ncol;
@@ -431,23 +431,24 @@ int coarse_layout(const Plan &p, Inst<T> *a) {
 // forms it.
 bool fold_of(const Plan &p) { return p.lv[0].rb && p.lc > 0; }
 
-// LDS of a blocked level's box (every plane), its per-plane tables and z-transfer tables.
-size_t tb_lds_bytes(const HostLevel &H, size_t w) {
-    return ((size_t)H.nz * kTbW * kTbW + 6 * (size_t)H.nz) * w + 2 * (size_t)H.nz * sizeof(int);
-}
-
-// Level l of p may be smoothed in blocks (k_pre_tb / k_post_tb): a red/black level
-// below the finest with launches of its own, small enough for its launches to be
-// latency-bound (the blocks recompute their rings), halved in x and y into the next,
-// tiles that divide both extents, no column twice in one box (extents of at least a
-// box edge), at most kTbMaxNz planes, and the box in kTbLdsBytes of LDS.
-bool tb_geom(const Plan &p, int l, size_t w) {
-    if (l < 1 || l >= p.lc) return false;
+// Level l of p may be smoothed in blocks (k_pre_tb / k_post_tb): a red/black level with
+// launches of its own, halved in x and y into the next, no column twice in one box (extents of
+// at least a box edge), at most kTbMaxNz planes, and at most kTbCells cells: the blocks recompute
+// their rings, so they win while a level's launches are latency-bound (128 x 128 x 60: a
+// block per compute unit) and lose where the cells stream from HBM.
+constexpr size_t kTbCells = (size_t)1 << 20;
+bool tb_geom(const Plan &p, int l) {
+    if (l >= p.lc) return false;
     const HostLevel &H = p.lv[l];
-    return H.rb && p.lv[l + 1].xy_from_finer == 1 && H.ncell() < ((size_t)1 << 18) && H.nx % kTbT == 0 &&
-           H.ny % kTbT == 0 && H.nx >= kTbW && H.ny >= kTbW && H.nz <= kTbMaxNz &&
-           tb_lds_bytes(H, w) <= (size_t)kTbLdsBytes &&
-           // the coarse values under a box fit above the interpolants (k_post_tb)
+    return H.rb && p.lv[l + 1].xy_from_finer == 1 && H.nx >= kTbW && H.ny >= kTbW && H.nz <= kTbMaxNz;
+}
+// Levels whose black values between the two launches have an array of their own; the others
+// use the finer level's red half or, on the finest level, e's black half.
+bool tb_own_array(const Plan &p, int l, size_t w) {
+    if (l < 1 || !tb_geom(p, l)) return false;
+    const HostLevel &H = p.lv[l];
+    return H.ncell() < ((size_t)1 << 18) && H.nx % kTbT == 0 && H.ny % kTbT == 0 && H.nz <= 30 &&
+           ((size_t)H.nz * kTbW * kTbW + 6 * (size_t)H.nz) * w + 2 * (size_t)H.nz * sizeof(int) <= 64 * 1024 &&
            (size_t)p.lv[l + 1].nz * (kTbW * kTbW + (kTbW / 2 + 2) * (kTbW / 2 + 2)) <= (size_t)H.nz * kTbW * kTbW;
 }
 
@@ -545,7 +546,7 @@ size_t carve(Engine *e, void *ws) {
             if (mixed) lay(h.L32[l], p.lv[l], 4);
             else lay(h.L64[l], p.lv[l], 8);
             const size_t w = mixed ? 4 : 8;
-            if (tb_geom(p, l, w)) {
+            if (tb_own_array(p, l, w)) {
                 void *ea = cv.take(p.lv[l].ncell() * w);
                 if (mixed) h.L32[l].ealt = (float *)ea;
                 else h.L64[l].ealt = (double *)ea;
@@ -600,7 +601,7 @@ fx_status build_work(Engine *e) {
     e->w_res.cell0 = mk([&](const InstHost &h) { const Plan &p = h.plan; return tiles3(p.nx, p.ny, nzc(p)); });
     e->w_res.cell2 = mk([&](const InstHost &h) { const Plan &p = h.plan; return fold_of(p) ? 0 : tiles3(p.nx, p.ny, nzc(p)); });
     e->w_sm.clear(); e->w_rs.clear(); e->w_pr.clear(); e->w_prc.clear(); e->prc_cz.clear();
-    e->w_tb.clear(); e->tb.clear(); e->tb_lds.clear();
+    e->w_tb.clear(); e->tb.clear(); e->tb_nz.clear(); e->tb_nzc.clear();
     const int cc_ok = env_int("FERROX_PROLONG_CC", 1) != 0;
     // the coarse-column prolongation: red/black fine level, x and y halved, z paired
     auto by_cc = [cc_ok](const Plan &p, int l) {
@@ -633,21 +634,22 @@ fx_status build_work(Engine *e) {
             return tiles3(C.nx, C.ny, (C.nz + cz - 1) / cz);
         }));
         // blocked smoothing where every instance that has this level qualifies
-        const size_t w = e->prec == FX_PREC_MIXED ? 4 : 8;
-        bool ok = e->fuse && env_int("FERROX_TB", 1) != 0 && e->nu1c <= 2 && e->nu2c <= 2;
-        bool any = false;
-        int lds = 0;
+        bool ok = e->fuse && env_int("FERROX_TB", 1) != 0 && (l == 0 ? e->nu1 <= 2 && e->nu2 <= 2 : e->nu1c <= 2 && e->nu2c <= 2);
+        int nz = 0, nzc = 0;
+        size_t cells = 0;
         for (const InstHost &h : e->in) {
             if (l >= h.plan.lc) continue;
-            any = true;
-            ok = ok && tb_geom(h.plan, l, w);
-            lds = std::max(lds, (int)tb_lds_bytes(h.plan.lv[l], w));
+            ok = ok && tb_geom(h.plan, l);
+            cells += h.plan.lv[l].ncell();
+            nz = std::max(nz, h.plan.lv[l].nz);
+            nzc = std::max(nzc, h.plan.lv[l + 1].nz);
         }
-        e->tb.push_back(ok && any);
-        e->tb_lds.push_back(lds);
+        e->tb.push_back(ok && nz > 0 && cells <= kTbCells);
+        e->tb_nz.push_back(nz);
+        e->tb_nzc.push_back(nzc);
         e->w_tb.push_back(mk([&](const InstHost &h) {
             if (!e->tb[l] || l >= h.plan.lc) return 0;
-            return (h.plan.lv[l].nx / kTbT) * (h.plan.lv[l].ny / kTbT);
+            return ((h.plan.lv[l].nx + kTbT - 1) / kTbT) * ((h.plan.lv[l].ny + kTbT - 1) / kTbT);
         }));
     }
     if (bad) return fail(FX_EINVAL, "a launch would exceed 2^30 tiles");
@@ -752,7 +754,7 @@ Inst<T> make_inst(const Engine *e, int i) {
         L.cxy = D[l].cxy; L.czm = D[l].czm; L.czp = D[l].czp; L.dg = D[l].dg;
         L.e = D[l].e; L.r = D[l].r; L.sig = D[l].sig;
         L.sig_lo = H.sig_lo; L.sig_hi = H.sig_hi;
-        L.ealt = D[l].ealt;
+        L.ealt = D[l].ealt ? D[l].ealt : (l > 0 ? D[l - 1].e : D[l].e + H.ncell() / 2);
         if (l + 1 < a.nlev) {
             XferArgs<T> &X = a.xf[l];
             X.cks = D[l + 1].ks; X.ccnt = D[l + 1].cnt;
@@ -881,6 +883,10 @@ void smooth_l(Engine *e, int l, int color, int zi, int upd, int skip_light = 0) 
     launch_smooth(idev<T>(e), w, l, color, zi, upd, e->scfg[l], pb, e->st, e0, e1, skip_light);
 }
 
+// Level l runs blocked (the probe times the finest level's half-sweeps one by one, so while it
+// is on that level keeps them; the same bits).
+bool blocked(const Engine *e, int l) { return e->tb[l] && !(l == 0 && e->probe); }
+
 // One V(nu1, nu2) cycle over every running instance.  Levels 0 .. lc-1 of an
 // instance have their own launches; the coarse kernel takes the rest.  On
 // the finest level the last black half-sweep also forms phi_out = phi_in +
@@ -889,8 +895,8 @@ template <typename T>
 void enq_vcycle(Engine *e) {
     const Inst<T> *I = idev<T>(e);
     for (int l = 0; l < e->max_lc; ++l) {
-        if (e->tb[l]) {                                  // sweeps and restriction in blocks
-            launch_pre_tb(I, e->w_tb[l], l, e->nu1c, e->tb_lds[l], e->st);
+        if (blocked(e, l)) {                             // sweeps and restriction in blocks
+            launch_pre_tb(I, e->w_tb[l], l, l == 0 ? e->nu1 : e->nu1c, e->tb_nz[l], e->st);
             continue;
         }
         const int nu1 = l == 0 ? e->nu1 : e->nu1c;
@@ -909,8 +915,8 @@ void enq_vcycle(Engine *e) {
     }
     launch_coarse(I, e->st_dev, e->n, e->lds_max, e->st);
     for (int l = e->max_lc - 1; l >= 0; --l) {
-        if (e->tb[l]) {                                  // prolongation and sweeps in blocks
-            launch_post_tb(I, e->w_tb[l], l, e->nu2c, e->tb_lds[l], e->st);
+        if (blocked(e, l)) {                             // prolongation and sweeps in blocks
+            launch_post_tb(I, e->w_tb[l], l, l == 0 ? e->nu2 : e->nu2c, e->tb_nz[l], e->tb_nzc[l], e->st);
             continue;
         }
         const int nu2 = l == 0 ? e->nu2 : e->nu2c;
