@@ -1661,8 +1661,10 @@ struct TbCells {
     T r[2][ZQ], iv[2][ZQ], cx[2][ZQ], cm[2][ZQ], cp[2][ZQ];
 
     // idg: room for the reciprocal diagonals of the planes without sigma, formed once per block
-    // (a division per cell cost 3 us a launch); its barrier also publishes the caller's stores.
-    __device__ __forceinline__ void load(const Lv<T, 1> &L, const TbCol &c, T FX_AS(3) *idg) {
+    // (a division per cell cost 3 us a launch); stores: LDS stores of the caller to be published
+    // by the same barrier, after this thread's loads have been issued.
+    template <typename F>
+    __device__ __forceinline__ void load(const Lv<T, 1> &L, const TbCol &c, T FX_AS(3) *idg, F stores) {
         const int plane = L.ny * (L.nx >> 1), half = plane * L.nz, hsz = plane * (L.sig_hi - L.sig_lo);
 #pragma unroll
         for (int col = 0; col < 2; ++col)
@@ -1674,6 +1676,7 @@ struct TbCells {
                 if (has_sig(L, k)) iv[col][z] = L.sig[col * hsz + (k - L.sig_lo) * plane + c.q0];
             }
         for (int k = threadIdx.x; k < L.nz; k += kTbThreads) idg[k] = T(1) / L.dg[k];
+        stores();
         __syncthreads();
 #pragma unroll
         for (int col = 0; col < 2; ++col)
@@ -1696,7 +1699,7 @@ struct TbCells {
     // One half-sweep of colour col over the box columns within ring R (ZI: from a zero
     // start).  Cells of one colour are not neighbours, so the new values of a group of cells
     // are formed before any of them is stored (the group bounds the registers held).
-    template <int ZI>
+    template <int ZI, int BAR = 1>
     __device__ __forceinline__ void half_sweep(const TbCol &c, int nz, T FX_AS(3) *box, int col, int R) const {
         constexpr int G = ZQ <= 4 ? ZQ : ZQ / 2;
         T FX_AS(3) *es = tb_array(box, c, col);
@@ -1717,7 +1720,7 @@ struct TbCells {
                 }
             }
         }
-        __syncthreads();
+        if (BAR) __syncthreads();
     }
 };
 
@@ -1738,7 +1741,7 @@ __global__ __launch_bounds__(kTbThreads) void k_pre_tb(const Inst<T> *I, Work w,
     const int nz = L.nz;
     tb_pads(box, c, nz);
     TbCells<T, ZQ> m;
-    m.load(L, c, box + 2 * c.np * kTbPl);
+    m.load(L, c, box + 2 * c.np * kTbPl, [] {});
     // sigma of the tile's coarse cells (kTbT/2 x kTbT/2 columns of every coarse plane)
     constexpr int kC = kTbT / 2;
     for (int u = threadIdx.x; u < kC * kC * (C.sig_hi - C.sig_lo); u += kTbThreads) {
@@ -1821,13 +1824,17 @@ __global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w
     // further on the side of its parity, as prolong_value takes them (wrapping included).
     T FX_AS(3) *cb = box + 2 * c.np * kTbPl;
     const int cx0 = c.tx * (kTbT / 2) - kTbH / 2 - 1, cy0 = c.ty * (kTbT / 2) - kTbH / 2 - 1;
-    for (int u = threadIdx.x; u < kTbCW * kTbCW * C.nz; u += kTbThreads) {
+    constexpr int CU = (kTbCW * kTbCW * ZQ * kTbShares + kTbThreads - 1) / kTbThreads;   // C.nz <= 4 ZQ
+    T cv[CU];
+#pragma unroll
+    for (int q = 0; q < CU; ++q) {
+        const int u = min((int)threadIdx.x + q * kTbThreads, kTbCW * kTbCW * C.nz - 1);
         const int K = u / (kTbCW * kTbCW), rem = u - K * kTbCW * kTbCW;
         const int cj = rem / kTbCW, ci = rem - cj * kTbCW;
         int I0 = cx0 + ci, J = cy0 + cj;
         I0 += I0 < 0 ? C.nx : (I0 >= C.nx ? -C.nx : 0);
         J += J < 0 ? C.ny : (J >= C.ny ? -C.ny : 0);
-        cb[u] = C.e[cidx(C, I0, J, K)];
+        cv[q] = C.e[cidx(C, I0, J, K)];
     }
     T eb[ZQ];
     const T FX_AS(1) *ea = asp<1>(a.lv[level].ealt);
@@ -1835,11 +1842,19 @@ __global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w
     for (int z = 0; z < ZQ; ++z) eb[z] = ea[min(tb_k(c, 1, z), nz - 1) * plane + c.q0];
     tb_pads(box, c, nz);
     TbCells<T, ZQ> m;
-    m.load(F, c, cb + kTbCW * kTbCW * C.nz);
+    m.load(F, c, cb + kTbCW * kTbCW * C.nz, [&] {
+#pragma unroll
+        for (int q = 0; q < CU; ++q) {
+            const int u = threadIdx.x + q * kTbThreads;
+            if (u < kTbCW * kTbCW * C.nz) cb[u] = cv[q];
+        }
+    });
     T FX_AS(3) *blk = tb_array(box, c, 1);
     if (c.ring <= 2 * nu) {
         // the correction of the black cells: lint_z of the lateral interpolants on the parent
-        // and neighbour planes (prolong_value's weights and operands)
+        // and neighbour planes (prolong_value's weights and operands).  The planes are paired,
+        // so cell z's parent is coarse plane z0 + z and its neighbour the next one up (odd
+        // planes) or down (even ones, b = 0): ZQ + 1 interpolants serve the share.
         const T wx[2] = {T(0.75), T(0.25)}, wy[2] = {T(0.75), T(0.25)};
         T wgt[2][2];
 #pragma unroll
@@ -1848,59 +1863,61 @@ __global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w
             for (int xx = 0; xx < 2; ++xx) wgt[yy][xx] = wx[xx] * wy[yy];
         const int gu = c.tx * kTbT - kTbH + c.bx, gv = c.ty * kTbT - kTbH + c.by;   // unwrapped
         const int ci = (gu >> 1) - cx0, cj = (gv >> 1) - cy0;
-        const int o[2][2] = {{cj * kTbCW + ci, cj * kTbCW + ci + ((gu & 1) ? 1 : -1)},
-                             {(cj + ((gv & 1) ? 1 : -1)) * kTbCW + ci,
-                              (cj + ((gv & 1) ? 1 : -1)) * kTbCW + ci + ((gu & 1) ? 1 : -1)}};
+        const int dx = (gu & 1) ? 1 : -1, dy = ((gv & 1) ? 1 : -1) * kTbCW, o = cj * kTbCW + ci;
+        const int b1 = (1 + c.par) & 1;
+        auto lateral = [&](int q) {
+            const int K = max(0, min(c.z0 + q - 1 + b1, C.nz - 1));
+            const T FX_AS(3) *p = cb + K * (kTbCW * kTbCW) + o;
+            T v[2][2];
+            v[0][0] = p[0];
+            v[0][1] = p[dx];
+            v[1][0] = p[dy];
+            v[1][1] = p[dy + dx];
+            return lint_xy<2, 2>(wgt, v);
+        };
+        T lo = lateral(0);
 #pragma unroll
         for (int z = 0; z < ZQ; ++z) {
+            const T hi = lateral(z + 1);
             const int kk = tb_k(c, 1, z), k = min(kk, nz - 1);
-            const int ka = X.pka[k], kb = X.pkb[k];
-            T sp[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const T FX_AS(3) *p = cb + (q == 0 || kb < 0 ? ka : kb) * (kTbCW * kTbCW);
-                T v[2][2];
-#pragma unroll
-                for (int yy = 0; yy < 2; ++yy)
-#pragma unroll
-                    for (int xx = 0; xx < 2; ++xx) v[yy][xx] = p[o[yy][xx]];
-                sp[q] = lint_xy<2, 2>(wgt, v);
-            }
-            const T v = eb[z] + lint_z(T(X.pwa[k]), sp[0], kb >= 0 ? T(X.pwb[k]) : T(0), sp[1]);
+            const int kb = X.pkb[k];
+            const T v = eb[z] + lint_z(T(X.pwa[k]), b1 ? lo : hi, kb >= 0 ? T(X.pwb[k]) : T(0), b1 ? hi : lo);
             if (kk < nz) blk[k * kTbPl] = v;
+            lo = hi;
         }
     }
     __syncthreads();
     m.template half_sweep<0>(c, nz, box, 0, 2 * nu - 1);
-    m.template half_sweep<0>(c, nz, box, 1, 2 * nu - 2);
     if (nu > 1) {
+        m.template half_sweep<0>(c, nz, box, 1, 2);
         m.template half_sweep<0>(c, nz, box, 0, 1);
-        m.template half_sweep<0>(c, nz, box, 1, 0);
     }
-    if (!c.own) return;
-    if (FINEST) {
-        const size_t off = (size_t)a.kb * a.nx * a.ny;
+    // phi of the tile's cells, in flight during the last half-sweep
+    const size_t off = (size_t)a.kb * a.nx * a.ny;
+    const int col0 = c.gj * F.nx + c.gi, nxy = F.nx * F.ny;
+    double ph[2][ZQ];
+    if (FINEST && c.own) {
         const double FX_AS(1) *phi_in = asp<1>(a.phi[cyc_src(st)]) + off;
-        double FX_AS(1) *phi_out = asp<1>(a.phi[cyc_dst(st)]) + off;
-        const int FX_AS(1) *pflags = asp<1>(a.pflags);
-        const int col0 = c.gj * F.nx + c.gi, nxy = F.nx * F.ny;
-        double ph[2][ZQ], lim[2][ZQ];
 #pragma unroll
         for (int col = 0; col < 2; ++col)
 #pragma unroll
-            for (int z = 0; z < ZQ; ++z) {
-                const int k = min(tb_k(c, col, z), nz - 1);
-                ph[col][z] = phi_in[(size_t)k * nxy + col0];
-                lim[col][z] = (pflags[k] & PF_SC) ? a.dmax : 1e300;
-            }
+            for (int z = 0; z < ZQ; ++z) ph[col][z] = phi_in[(size_t)min(tb_k(c, col, z), nz - 1) * nxy + col0];
+    }
+    // each thread reads back its own cells alone: no barrier
+    m.template half_sweep<0, 0>(c, nz, box, 1, 0);
+    if (!c.own) return;
+    if (FINEST) {
+        double FX_AS(1) *phi_out = asp<1>(a.phi[cyc_dst(st)]) + off;
+        const int FX_AS(1) *pflags = asp<1>(a.pflags);
 #pragma unroll
         for (int col = 0; col < 2; ++col)
 #pragma unroll
             for (int z = 0; z < ZQ; ++z) {
                 const int k = tb_k(c, col, z);
                 if (k >= nz) continue;
+                const double lim = (pflags[k] & PF_SC) ? a.dmax : 1e300;
                 const double d = (double)tb_array(box, c, col)[k * kTbPl];
-                phi_out[(size_t)k * nxy + col0] = ph[col][z] + fmin(fmax(d, -lim[col][z]), lim[col][z]);
+                phi_out[(size_t)k * nxy + col0] = ph[col][z] + fmin(fmax(d, -lim), lim);
             }
     } else {
 #pragma unroll
