@@ -333,6 +333,11 @@ struct Engine {
     std::vector<InstState> mir_plain;
     int no_alloc = 0;                   // allocates no device or pinned memory (poisson_solve_static)
     int *prefix_dev = nullptr;
+    // the region of the workspace that holds what the host writes at set-up (per-plane tables,
+    // instances, states, tile counts), and its host copy while it is being written
+    char *tab_dev = nullptr;
+    size_t tab_off = 0, tab_bytes = 0;
+    std::vector<char> tab_host;
     double *sched_dev = nullptr;        // n x kSchedChunk gate potentials
     double *probe_dev = nullptr;        // kProbeMax byte counters
     double *qv_out = nullptr;           // n x (Q, V_fe) of the current state
@@ -517,30 +522,13 @@ size_t carve(Engine *e, void *ws) {
         h.P[1] = (double *)cv.take(nfull * sizeof(double));
         const int nbuf = h.d.time_order == 2 ? kPhiBufs : kPhiBufs - 2;
         for (int b = 1; b < nbuf; ++b) h.phi[b] = (double *)cv.take(nfull * sizeof(double));
-        const int nzd = p.nzd;
-        h.t_cxy = (double *)cv.take(nzd * sizeof(double));
-        h.t_czm = (double *)cv.take(nzd * sizeof(double));
-        h.t_czp = (double *)cv.take(nzd * sizeof(double));
-        h.t_wl = (double *)cv.take(nzd * sizeof(double));
-        h.t_wr = (double *)cv.take(nzd * sizeof(double));
-        h.t_p0e = (double *)cv.take(nzd * sizeof(double));
-        h.t_n0e = (double *)cv.take(nzd * sizeof(double));
-        h.t_fd = (double *)cv.take(4 * (size_t)nzd * sizeof(double));
-        h.t_flags = (int *)cv.take(nzd * sizeof(int));
         const int nlev = (int)p.lv.size();
         h.L64.assign(mixed ? 0 : nlev, DevLevel<double>());
         h.L32.assign(mixed ? nlev : 0, DevLevel<float>());
         auto lay = [&](auto &D, const HostLevel &H, size_t w) {
             using TT = std::remove_pointer_t<decltype(D.e)>;
             const size_t nc = H.ncell(), ns = H.nsig();
-            const int nz = H.nz;
             D.e = (TT *)cv.take(nc * w); D.r = (TT *)cv.take(nc * w); D.sig = (TT *)cv.take(std::max<size_t>(ns, 1) * w);
-            D.cxy = (TT *)cv.take(nz * w); D.czm = (TT *)cv.take(nz * w);
-            D.czp = (TT *)cv.take(nz * w); D.dg = (TT *)cv.take(nz * w);
-            D.pwa = (TT *)cv.take(nz * w); D.pwb = (TT *)cv.take(nz * w);
-            D.ks = (int *)cv.take(nz * sizeof(int)); D.cnt = (int *)cv.take(nz * sizeof(int));
-            D.thick = (int *)cv.take(nz * sizeof(int)); D.pka = (int *)cv.take(nz * sizeof(int));
-            D.pkb = (int *)cv.take(nz * sizeof(int));
         };
         for (int l = 0; l < nlev; ++l) {
             if (mixed) lay(h.L32[l], p.lv[l], 4);
@@ -558,15 +546,52 @@ size_t carve(Engine *e, void *ws) {
         h.qv_part = (double *)cv.take(2 * kQvBlocks * sizeof(double));
         h.qv_rec = (double *)cv.take(2 * (size_t)kRecSteps * sizeof(double));
     }
+    // everything the host writes lies together: one copy uploads it (a blocking copy takes
+    // about 12 us whatever its size, and a stack has some hundred tables)
+    e->tab_dev = (char *)cv.take(0);
+    e->tab_off = cv.off;
+    for (InstHost &h : e->in) {
+        const Plan &p = h.plan;
+        const int nzd = p.nzd;
+        h.t_cxy = (double *)cv.take(nzd * sizeof(double));
+        h.t_czm = (double *)cv.take(nzd * sizeof(double));
+        h.t_czp = (double *)cv.take(nzd * sizeof(double));
+        h.t_wl = (double *)cv.take(nzd * sizeof(double));
+        h.t_wr = (double *)cv.take(nzd * sizeof(double));
+        h.t_p0e = (double *)cv.take(nzd * sizeof(double));
+        h.t_n0e = (double *)cv.take(nzd * sizeof(double));
+        h.t_fd = (double *)cv.take(4 * (size_t)nzd * sizeof(double));
+        h.t_flags = (int *)cv.take(nzd * sizeof(int));
+        auto lay = [&](auto &D, const HostLevel &H, size_t w) {
+            using TT = std::remove_pointer_t<decltype(D.e)>;
+            const int nz = H.nz;
+            D.cxy = (TT *)cv.take(nz * w); D.czm = (TT *)cv.take(nz * w);
+            D.czp = (TT *)cv.take(nz * w); D.dg = (TT *)cv.take(nz * w);
+            D.pwa = (TT *)cv.take(nz * w); D.pwb = (TT *)cv.take(nz * w);
+            D.ks = (int *)cv.take(nz * sizeof(int)); D.cnt = (int *)cv.take(nz * sizeof(int));
+            D.thick = (int *)cv.take(nz * sizeof(int)); D.pka = (int *)cv.take(nz * sizeof(int));
+            D.pkb = (int *)cv.take(nz * sizeof(int));
+        };
+        for (size_t l = 0; l < p.lv.size(); ++l) {
+            if (mixed) lay(h.L32[l], p.lv[l], 4);
+            else lay(h.L64[l], p.lv[l], 8);
+        }
+    }
     const size_t inst_bytes = mixed ? sizeof(Inst<float>) : sizeof(Inst<double>);
     e->inst_dev = cv.take((size_t)e->n * inst_bytes);
     e->st_dev = (InstState *)cv.take((size_t)e->n * sizeof(InstState));
     const size_t ntab = 4 + 5 * (size_t)e->max_lc;
     e->prefix_dev = (int *)cv.take(ntab * (e->n + 1) * sizeof(int));
+    e->tab_bytes = cv.off - e->tab_off;
     e->sched_dev = (double *)cv.take((size_t)e->n * kSchedChunk * sizeof(double));
     e->probe_dev = (double *)cv.take(kProbeMax * sizeof(double));
     e->qv_out = (double *)cv.take(2 * (size_t)e->n * sizeof(double));
     return cv.off + 256;
+}
+
+// Write `bytes` of a table into the host copy of the table region (dst: its device address).
+void put_table(Engine *e, const void *dst, const void *src, size_t bytes) {
+    memcpy(e->tab_host.data() + ((const char *)dst - e->tab_dev), src, bytes);
 }
 
 // Prefix tables of per-instance tile counts, one per launch kind.
@@ -653,35 +678,36 @@ fx_status build_work(Engine *e) {
         }));
     }
     if (bad) return fail(FX_EINVAL, "a launch would exceed 2^30 tiles");
-    HIP_OK(hipMemcpy(e->prefix_dev, e->prefix_host.data(), e->prefix_host.size() * sizeof(int), hipMemcpyHostToDevice));
+    put_table(e, e->prefix_dev, e->prefix_host.data(), e->prefix_host.size() * sizeof(int));
     return FX_OK;
 }
 
 template <typename T>
-fx_status upload_level(const HostLevel &H, DevLevel<T> &D) {
+void put_level(Engine *e, const HostLevel &H, const DevLevel<T> &D) {
     std::vector<T> a(H.nz);
-    auto up = [&](T *dst, const std::vector<double> &src) -> fx_status {
+    auto up = [&](T *dst, const std::vector<double> &src) {
         for (int K = 0; K < H.nz; ++K) a[K] = (T)src[K];
-        HIP_OK(hipMemcpy(dst, a.data(), H.nz * sizeof(T), hipMemcpyHostToDevice));
-        return FX_OK;
+        put_table(e, dst, a.data(), H.nz * sizeof(T));
     };
-    auto upi = [&](int *dst, std::vector<int> v, int fillv) -> fx_status {
+    auto upi = [&](int *dst, std::vector<int> v, int fillv) {
         v.resize(H.nz, fillv);
-        HIP_OK(hipMemcpy(dst, v.data(), H.nz * sizeof(int), hipMemcpyHostToDevice));
-        return FX_OK;
+        put_table(e, dst, v.data(), H.nz * sizeof(int));
     };
-    fx_status st;
-    if ((st = up(D.cxy, H.cxy)) || (st = up(D.czm, H.czm)) || (st = up(D.czp, H.czp)) || (st = up(D.dg, H.dg)))
-        return st;
+    up(D.cxy, H.cxy);
+    up(D.czm, H.czm);
+    up(D.czp, H.czp);
+    up(D.dg, H.dg);
     std::vector<double> pwa(H.pwa), pwb(H.pwb);
     pwa.resize(H.nz, 1.0); pwb.resize(H.nz, 0.0);
-    if ((st = up(D.pwa, pwa)) || (st = up(D.pwb, pwb))) return st;
+    up(D.pwa, pwa);
+    up(D.pwb, pwb);
     std::vector<int> thick(H.nz);
     for (int K = 0; K < H.nz; ++K) thick[K] = H.e0[K] - H.s0[K];
-    if ((st = upi(D.ks, H.ks, 0)) || (st = upi(D.cnt, H.cnt, 1)) || (st = upi(D.thick, thick, 1)) ||
-        (st = upi(D.pka, H.pka, 0)) || (st = upi(D.pkb, H.pkb, -1)))
-        return st;
-    return FX_OK;
+    upi(D.ks, H.ks, 0);
+    upi(D.cnt, H.cnt, 1);
+    upi(D.thick, thick, 1);
+    upi(D.pka, H.pka, 0);
+    upi(D.pkb, H.pkb, -1);
 }
 
 template <typename T>
@@ -828,26 +854,23 @@ fx_status upload_all(Engine *e) {
             }
         }
         const HostLevel &H0 = p.lv[0];
-        HIP_OK(hipMemcpy(h.t_cxy, H0.cxy.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_czm, H0.czm.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_czp, H0.czp.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_wl, wl.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_wr, wr.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_p0e, p0e.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_n0e, n0e.data(), nzd * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_fd, fdt.data(), fdt.size() * sizeof(double), hipMemcpyHostToDevice));
-        HIP_OK(hipMemcpy(h.t_flags, fl.data(), nzd * sizeof(int), hipMemcpyHostToDevice));
+        put_table(e, h.t_cxy, H0.cxy.data(), nzd * sizeof(double));
+        put_table(e, h.t_czm, H0.czm.data(), nzd * sizeof(double));
+        put_table(e, h.t_czp, H0.czp.data(), nzd * sizeof(double));
+        put_table(e, h.t_wl, wl.data(), nzd * sizeof(double));
+        put_table(e, h.t_wr, wr.data(), nzd * sizeof(double));
+        put_table(e, h.t_p0e, p0e.data(), nzd * sizeof(double));
+        put_table(e, h.t_n0e, n0e.data(), nzd * sizeof(double));
+        put_table(e, h.t_fd, fdt.data(), fdt.size() * sizeof(double));
+        put_table(e, h.t_flags, fl.data(), nzd * sizeof(int));
         const std::vector<DevLevel<T>> &D = levels<T>(h);
-        for (size_t l = 0; l < p.lv.size(); ++l) {
-            fx_status st = upload_level(p.lv[l], const_cast<DevLevel<T> &>(D[l]));
-            if (st) return st;
-        }
+        for (size_t l = 0; l < p.lv.size(); ++l) put_level(e, p.lv[l], D[l]);
         host[i] = make_inst<T>(e, i);
         h.lds = host[i].lds_bytes;
         if (h.lds > kCoarseLdsBytes) return fail(FX_EINVAL, "coarse levels need %d bytes of LDS", h.lds);
         e->lds_max = std::max(e->lds_max, h.lds);
     }
-    HIP_OK(hipMemcpy(e->inst_dev, host.data(), (size_t)e->n * sizeof(Inst<T>), hipMemcpyHostToDevice));
+    put_table(e, e->inst_dev, host.data(), (size_t)e->n * sizeof(Inst<T>));
     for (int i = 0; i < e->n; ++i) {
         InstState &s = e->mir[i];
         memset(&s, 0, sizeof s);
@@ -858,7 +881,9 @@ fx_status upload_all(Engine *e) {
         s.parked = 1;
         s.v_top = e->in[i].d.v_top;
     }
-    HIP_OK(hipMemcpy(e->st_dev, e->mir, (size_t)e->n * sizeof(InstState), hipMemcpyHostToDevice));
+    put_table(e, e->st_dev, e->mir, (size_t)e->n * sizeof(InstState));
+    HIP_OK(hipMemcpy(e->tab_dev, e->tab_host.data(), e->tab_bytes, hipMemcpyHostToDevice));
+    e->tab_host = std::vector<char>();
     return FX_OK;
 }
 
@@ -1030,6 +1055,19 @@ fx_status solve_plain_t(Engine *e) {
     int enq = 0;
     int batch = e->trace ? 0 : std::max(1, e->k_pred);
     fx_status st;
+    // cycles an instance still needs, from its contraction so far (at the first check measured
+    // against ||f||); checking after every cycle left the GPU idle for a round trip each
+    std::vector<double> last(e->n, 0.0);
+    std::vector<int> at(e->n, 0);
+    auto more = [&](int i) {
+        const InstState &c = e->mir[i];
+        const double tol = e->in[i].d.tol_rel, from = at[i] > 0 ? last[i] : c.fn2;
+        const int n = c.cycles - at[i];
+        const double rate = n > 0 && c.rn2 > 0 && from > c.rn2 ? std::log(from / c.rn2) / n : 0.0;
+        last[i] = c.rn2;
+        at[i] = c.cycles;
+        return rate > 0 ? std::log(c.rn2 / (tol * tol * c.fn2)) / rate : 1.0;
+    };
     for (;;) {
         for (int q = 0; q < batch && enq < e->max_cycles; ++q, ++enq) enq_cycle<T>(e, 0);
         if ((st = read_states(e))) return st;
@@ -1042,6 +1080,8 @@ fx_status solve_plain_t(Engine *e) {
         if (all) break;
         if (enq >= e->max_cycles) return fail(FX_EDEVICE, "solver state did not stop after %d cycles", enq);
         batch = 1;
+        for (int i = 0; i < e->n && !e->trace; ++i)
+            if (!e->mir[i].done) batch = std::max(batch, (int)std::ceil(std::min(8.0, more(i)) - 0.2));
     }
     launch_head(I, e->st_dev, e->n, 0, e->st);
     if ((st = read_states(e))) return st;
@@ -1242,16 +1282,20 @@ fx_status engine_init(Engine *e, double *const *d_P, double *const *d_phi, void 
     } else if (hipHostMalloc((void **)&e->mir, (size_t)e->n * sizeof(InstState), 0) != hipSuccess) {
         return fail(FX_EDEVICE, "hipHostMalloc failed");
     }
+    e->tab_host.assign(e->tab_bytes, 0);
     fx_status st = build_work(e);
     if (st) return st;
     st = e->prec == FX_PREC_MIXED ? upload_all<float>(e) : upload_all<double>(e);
     if (st) return st;
+    // the fields and level arrays of every instance start at zero (phi^{0,(0)} = 0, P off the
+    // ferroelectric; the autotuner may sweep the levels before any solve): one launch over
+    // the workspace ahead of the tables
+    launch_zero(d_ws, e->tab_off, e->st);
     for (int i = 0; i < e->n; ++i) {
         InstHost &h = e->in[i];
         const Plan &p = h.plan;
-        // P: zero off the ferroelectric in both buffers
+        // P: zero off the ferroelectric in the caller's array
         const size_t nfull = (size_t)p.nx * p.ny * p.nz, nxy = (size_t)p.nx * p.ny;
-        launch_fill(h.P[1], nfull, 0.0, e->st);
         if (p.f0 >= 0) {
             if (p.f0 > 0) launch_fill(h.P[0], (size_t)p.f0 * nxy, 0.0, e->st);
             if (p.f1 < p.nz) launch_fill(h.P[0] + (size_t)p.f1 * nxy, (size_t)(p.nz - p.f1) * nxy, 0.0, e->st);
@@ -1259,19 +1303,7 @@ fx_status engine_init(Engine *e, double *const *d_P, double *const *d_phi, void 
             launch_fill(h.P[0], nfull, 0.0, e->st);
         }
         // Step 0: phi^{0,(0)} = 0, then solve
-        for (int b = 0; b < kPhiBufs; ++b)
-            if (h.phi[b]) launch_fill(h.phi[b], nfull, 0.0, e->st);
-        // level arrays start defined (the autotuner may sweep them before any solve)
-        const size_t w = e->prec == FX_PREC_MIXED ? sizeof(float) : sizeof(double);
-        for (size_t l = 0; l < p.lv.size(); ++l) {
-            const HostLevel &H = p.lv[l];
-            void *ee = e->prec == FX_PREC_MIXED ? (void *)h.L32[l].e : (void *)h.L64[l].e;
-            void *rr = e->prec == FX_PREC_MIXED ? (void *)h.L32[l].r : (void *)h.L64[l].r;
-            void *ss = e->prec == FX_PREC_MIXED ? (void *)h.L32[l].sig : (void *)h.L64[l].sig;
-            launch_zero(ee, H.ncell() * w, e->st);
-            launch_zero(rr, H.ncell() * w, e->st);
-            launch_zero(ss, std::max<size_t>(H.nsig(), 1) * w, e->st);
-        }
+        launch_fill(h.phi[0], nfull, 0.0, e->st);
         fill_contacts(e, i, true);
     }
     launch_fill(e->probe_dev, kProbeMax, 0.0, e->st);

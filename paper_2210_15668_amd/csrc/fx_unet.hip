@@ -16,9 +16,10 @@
 // (cin <-> cout): the adjoint of "read x at v + d" is "write to v + d", and
 // the periodic x-y wrap and the zeros beyond the z-ends are their own adjoints
 // under the flip.  The weight gradient sums dZ[v][cout] x[v + d][cin] over all
-// voxels (fx_unet_wgrad.hip).
+// voxels (fx_unet_wgrad.h).
 #include "fx_internal.h"
 #include "fx_unet_internal.h"
+#include "fx_unet_wgrad.h"
 #include "../../include/ferrox_unet.h"
 
 #include <cmath>

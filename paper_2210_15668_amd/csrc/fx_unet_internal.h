@@ -52,14 +52,4 @@ bool convz_forward(int ca, bool upa, int cb, int cout, int out, const bf16_t *XA
                    const bf16_t *wz, const float *bias, bf16_t *Y, int ldy, float *Pf, const float *hw, bf16_t *Yp,
                    int nx, int ny, int nz, hipStream_t st);
 
-// Weight gradient W[27][cout][cin] and, after it, bias gradient [cout] of a convolution into
-// dst, from its input X (leading dimension ldx; xl = 4: four channels present, the rest of cin
-// zero) and its BF16 output gradient G ([n][cout]); part: wgrad_part_floats(...) floats
-// (fx_unet_wgrad.hip).
-size_t wgrad_part_floats(int cin, int cout, int nx, int ny, int nz);
-void wgrad(int cin, int cout, int xl, const bf16_t *X, int ldx, const bf16_t *G, int nx, int ny, int nz, float *part,
-           float *dst, hipStream_t st);
-// dst[i] = sum over p < nparts of part[p][i], i < m, in a fixed order.
-void part_sum(const float *part, int nparts, int m, float *dst, hipStream_t st);
-
 }  // namespace fx

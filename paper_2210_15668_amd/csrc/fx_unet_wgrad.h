@@ -17,6 +17,8 @@
 // At 128 x 128 x 60 the ten layers take 0.28 ms and their partial sums 0.05 ms; a block per tap,
 // staging both operands again (transposed with 2-byte LDS stores), took 3.04 ms, its sums and the
 // bias sums 1.07 ms (loss and gradient 5.21 -> 1.43 ms).
+#pragma once
+
 #include "fx_internal.h"
 #include "fx_unet_internal.h"
 
@@ -300,10 +302,14 @@ void wg_tile(int tx, const bf16_t *X, int ldx, const bf16_t *G, const WgGeom &g,
 
 }  // namespace
 
+// dst[i] = sum over p < nparts of part[p][i], i < m, in a fixed order.
 void part_sum(const float *part, int nparts, int m, float *dst, hipStream_t st) {
     hipLaunchKernelGGL(k_wsum, dim3((m + 63) / 64), dim3(1024), 0, st, part, nparts, m, dst);
 }
 
+// Weight gradient W[27][cout][cin] and, after it, bias gradient [cout] of a convolution into
+// dst, from its input X (leading dimension ldx; xl = 4: four channels present, the rest of cin
+// zero) and its BF16 output gradient G ([n][cout]); part: wgrad_part_floats(...) floats.
 size_t wgrad_part_floats(int cin, int cout, int nx, int ny, int nz) {
     int nparts;
     (void)wg_geom(cin, cout, nx, ny, nz, &nparts);
