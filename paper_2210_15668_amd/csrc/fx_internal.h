@@ -55,6 +55,10 @@ constexpr int kPhiBufs = 8;       // phi^n, up to 3 stored levels, two iterate b
                                   // the last predictor's phi*
 constexpr int kMaxHist = 4;       // stored levels of a predictor-corrector instance (Euler: 3)
 constexpr int kCoarseLdsBytes = 64 * 1024;
+// A plainly stored level (odd x or y) takes 16 launches a sweep pair and is not smoothed in
+// blocks: such levels join the coarse kernel up to this much LDS and this many cells.
+constexpr int kCoarseNatLds = 152 * 1024;
+constexpr int kCoarseNatCells = 4096;
 // temporal blocking of the smoothing (k_pre_tb / k_post_tb)
 constexpr int kTbT = 8;                    // tile edge (cells)
 constexpr int kTbH = 4;                    // ring (cells): 2 nu for nu <= 2 sweeps
@@ -185,9 +189,10 @@ struct Inst {
     int nu1, nu2, lds_bytes;
     int off_e[kMaxLevels], off_r[kMaxLevels], off_s[kMaxLevels], off_t[kMaxLevels];
     int off_x[kMaxLevels];             // transfer tables between coarse-kernel levels q and q+1
-    // conjugate-gradient bottom solve: search direction and two reduction scratch areas (LDS offsets)
+    // conjugate-gradient bottom solve: shared vector, reduction scratch (LDS offsets)
     int off_p, off_q, off_red;
     int bottom_iters;
+    int wave_lev;                      // first coarse-kernel level run by one wave (levels from lc; nlev - lc: none)
     double bottom_tol2;
 };
 

@@ -1953,30 +1953,62 @@ __device__ __forceinline__ void split_c(int c, const Split3 &s, int &i, int &j, 
 }
 
 constexpr int kCoarseThreads = 1024;
+// First thread of this wave.  Waves without cells on a level skip its phases (but not the
+// barriers): the arithmetic of fifteen idle waves would hold up the one that has some.
+__device__ __forceinline__ int wave_first() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63); }
 
-// A coarse-kernel phase: the whole workgroup works on the level's cells, and a workgroup
-// barrier separates it from the next phase.  A phase is latency: one chain of LDS reads,
-// FP64 arithmetic and a store, so what a thread needs of its cells for all sweeps of a level
-// (right-hand sides, reciprocal diagonals, coefficients, neighbour offsets) is worked out
-// once and held in registers.
+// The workers of a level: the whole workgroup, or (W = 1) its first wave alone, where a level and
+// everything below it fit a wave; its LDS accesses complete in order, so a phase needs no
+// barrier there.
+template <int W>
+struct Crew {
+    static constexpr int size = W ? 64 : kCoarseThreads;
+    static __device__ __forceinline__ void sync() {
+        if (W) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+            __syncthreads();
+        }
+    }
+};
+
+// 1 / x for a positive normal x, to within a rounding or two of the quotient (hardware
+// estimate and Newton steps).  A division is about 400 cycles of latency, this 100; the coarse
+// levels need no kernel's bits but their own.
+__device__ __forceinline__ double rcp_newton(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+    return __builtin_fma(y, __builtin_fma(-x, y, 1.0), y);
+}
+__device__ __forceinline__ float rcp_newton(float x) { return 1.0f / x; }
+
+// A coarse-kernel phase: the crew works on the level's cells, and a barrier separates it from
+// the next phase.  A phase is latency: one chain of LDS reads, FP64 arithmetic and a store, so
+// what a thread needs of its cells for all sweeps of a level (right-hand sides, reciprocal
+// diagonals, coefficients, neighbour offsets) is worked out once and held in registers.
 //
 // Red/black level: NP storage pairs (a red and a black cell of one row) per thread.  The
 // pair's red and black cells are each other's x neighbours; their other x neighbour lies in
 // the pair dx away, the y and z neighbours in pairs oy, oz away (all in the other colour's
 // array).  Absent neighbours (z-ends, ny = 1) weigh 0 and point at the pair itself.
-template <typename T, int NP>
+template <typename T, int NP, int W>
 struct RbCells {
-    T r[2][NP], iv[2][NP], cx[NP], cy[NP], cm[NP], cp[NP];
+    T r[2][NP], iv[2][NP], cx[NP], cy[NP], cm[NP], cp[NP], d0[NP];
     int q[NP], dx[2][NP], oy[2][NP], oz[2][NP];
     bool on[NP];
+    bool act;                                          // this wave has cells
 
     __device__ __forceinline__ void load(const Lv<T, 3> &L) {
         const int hx = L.nx >> 1, plane = hx * L.ny, n = plane * L.nz;
         const int hsz = plane * (L.sig_hi - L.sig_lo);
+        act = W || wave_first() < n;
+        if (!act) return;
         const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const int c = threadIdx.x + p * kCoarseThreads;
+            const int c = threadIdx.x + p * Crew<W>::size;
             on[p] = c < n;
             q[p] = on[p] ? c : 0;
             int m, j, k;
@@ -1999,7 +2031,8 @@ struct RbCells {
                 r[c2][p] = L.r[c2 * n + q[p]];
                 T d = L.dg[k];
                 if (hs) d += L.sig[c2 * hsz + q[p] - L.sig_lo * plane];
-                iv[c2][p] = T(1) / d;
+                if (c2 == 0) d0[p] = d;
+                iv[c2][p] = rcp_newton(d);
             }
         }
     }
@@ -2012,47 +2045,46 @@ struct RbCells {
         const int n = (L.nx >> 1) * L.ny * L.nz;
         T FX_AS(3) *es = L.e + c2 * n;
         const T FX_AS(3) *eo = L.e + (1 - c2) * n;
-        T v[NP];
+        if (act) {
+            T v[NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) v[p] = (zero_init ? r[c2][p] : r[c2][p] + nb(eo, c2, p)) * iv[c2][p];
+            for (int p = 0; p < NP; ++p) v[p] = (zero_init ? r[c2][p] : r[c2][p] + nb(eo, c2, p)) * iv[c2][p];
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
-            if (on[p]) es[q[p]] = v[p];
-        __syncthreads();
+            for (int p = 0; p < NP; ++p)
+                if (on[p]) es[q[p]] = v[p];
+        }
+        Crew<W>::sync();
     }
     // the red cells' residual into their own e (dead until the next red half-sweep)
     __device__ __forceinline__ void red_residual(const Lv<T, 3> &L) const {
-        const int hx = L.nx >> 1, plane = hx * L.ny, n = plane * L.nz;
-        const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
-        T v[NP];
+        const int n = (L.nx >> 1) * L.ny * L.nz;
+        if (act) {
+            T v[NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            const int k = fquo(fquo(q[p], sp.fx), sp.fy);
-            T d = L.dg[k];
-            if (k >= L.sig_lo && k < L.sig_hi) d += L.sig[q[p] - L.sig_lo * plane];
-            v[p] = res_value(r[0][p], d, L.e[q[p]], nb(L.e + n, 0, p));
+            for (int p = 0; p < NP; ++p) v[p] = res_value(r[0][p], d0[p], L.e[q[p]], nb(L.e + n, 0, p));
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if (on[p]) L.e[q[p]] = v[p];
         }
-#pragma unroll
-        for (int p = 0; p < NP; ++p)
-            if (on[p]) L.e[q[p]] = v[p];
-        __syncthreads();
+        Crew<W>::sync();
     }
 };
 
 // Restriction of a red/black level halved in x and y from the red residuals just formed: the
 // red child of row (j, k) of coarse column I is the red cell of pair I of that row.
-template <typename T, typename X_>
+template <int W, typename T, typename X_>
 __device__ __forceinline__ void restrict_pairs(const Lv<T, 3> &F, const Lv<T, 3> &C, const X_ &X) {
     const int hx = F.nx >> 1, n = C.nx * C.ny * C.nz;
     const Split3 sp{fdiv_of(C.nx), fdiv_of(C.ny)};
-    for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
+    for (int c = threadIdx.x; c < n; c += Crew<W>::size) {
         int I, J, K;
         split_c(c, sp, I, J, K);
         const int ks = X.cks[K], cnt = X.ccnt[K];
+        const double it = rcp_newton((double)X.cthick[K]);
         double sr = 0.0, ss = 0.0;
         for (int dz = 0; dz < cnt; ++dz) {
             const int k = ks + dz;
-            const double wz = (double)X.fthick[k] / (double)X.cthick[K];
+            const double wz = (double)X.fthick[k] * it;
 #pragma unroll
             for (int dy = 0; dy < 2; ++dy) {
                 const int j = 2 * J + dy;
@@ -2066,12 +2098,12 @@ __device__ __forceinline__ void restrict_pairs(const Lv<T, 3> &F, const Lv<T, 3>
         C.r[cidx(C, I, J, K)] = (T)(sr * 0.25);
         if (has_sig(C, K)) C.sig[sidx(C, I, J, K)] = (T)(ss * 0.25);
     }
-    __syncthreads();
+    Crew<W>::sync();
 }
 
-template <typename T, int NP, typename X_>
+template <typename T, int NP, int W, typename X_>
 __device__ __forceinline__ void co_pre_rb(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
-    RbCells<T, NP> c;
+    RbCells<T, NP, W> c;
     c.load(L);
     for (int s = 0; s < nu; ++s) {
         c.half_sweep(L, 0, s == 0);
@@ -2079,12 +2111,12 @@ __device__ __forceinline__ void co_pre_rb(const Lv<T, 3> &L, const Lv<T, 3> &C, 
     }
     if (X.xy == 1) {
         c.red_residual(L);
-        restrict_pairs(L, C, X);
+        restrict_pairs<W>(L, C, X);
     }
 }
-template <typename T, int NP>
+template <typename T, int NP, int W>
 __device__ __forceinline__ void co_post_rb(const Lv<T, 3> &L, int nu) {
-    RbCells<T, NP> c;
+    RbCells<T, NP, W> c;
     c.load(L);
     for (int s = 0; s < nu; ++s) {
         c.half_sweep(L, 0, 0);
@@ -2092,18 +2124,23 @@ __device__ __forceinline__ void co_post_rb(const Lv<T, 3> &L, int nu) {
     }
 }
 
-// Plainly stored level: NP cells per thread, each of one of the four colours.
-template <typename T, int NP>
+// Plainly stored level: NP cells per thread, each of one of the four colours.  With x and y both
+// odd the corner cell of a plane shares its colour with two of its periodic neighbours: a
+// barrier between the values and their stores then keeps the sweep reproducible.
+template <typename T, int NP, int W>
 struct NatCells {
     T r[NP], iv[NP], cx[NP], cm[NP], cp[NP];
     int c[NP], ox[2][NP], oy[2][NP], oz[2][NP], col[NP];   // col -1: no cell
+    bool act;                                              // this wave has cells
 
     __device__ __forceinline__ void load(const Lv<T, 3> &L) {
         const int plane = L.nx * L.ny, n = plane * L.nz;
+        act = W || wave_first() < n;
+        if (!act) return;
         const Split3 sp{fdiv_of(L.nx), fdiv_of(L.ny)};
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            const int cc = threadIdx.x + p * kCoarseThreads;
+            const int cc = threadIdx.x + p * Crew<W>::size;
             const bool on = cc < n;
             c[p] = on ? cc : 0;
             int i, j, k;
@@ -2119,72 +2156,89 @@ struct NatCells {
             cm[p] = k > 0 ? L.czm[k] : T(0);
             cp[p] = k < L.nz - 1 ? L.czp[k] : T(0);
             r[p] = L.r[c[p]];
-            iv[p] = T(1) / diag_of(L, i, j, k);
+            iv[p] = rcp_newton(diag_of(L, i, j, k));
         }
     }
     __device__ __forceinline__ void sweep(const Lv<T, 3> &L, int zero_init) const {
         const T wx = L.nx > 1 ? T(1) : T(0), wy = L.ny > 1 ? T(1) : T(0);
+        const bool corner = (L.nx & L.ny & 1) != 0;
         for (int color = 0; color < 4; ++color) {
             const int zi = zero_init && color == 0;
+            T v[NP];
+            if (act) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                if (col[p] == color) {
+                for (int p = 0; p < NP; ++p) {
+                    v[p] = T(0);
+                    if (col[p] != color) continue;
                     T s = 0;
                     if (!zi) {
                         const T FX_AS(3) *e = L.e + c[p];
                         const T x = wx * (e[ox[0][p]] + e[ox[1][p]]), y = wy * (e[oy[0][p]] + e[oy[1][p]]);
                         s = fmad(cp[p], e[oz[1][p]], fmad(cm[p], e[oz[0][p]], fmad(cx[p], y, cx[p] * x)));
                     }
-                    L.e[c[p]] = (r[p] + s) * iv[p];
-                } else if (zi && col[p] >= 0) {
-                    L.e[c[p]] = T(0);
+                    v[p] = (r[p] + s) * iv[p];
                 }
             }
-            __syncthreads();
+            if (corner) Crew<W>::sync();
+            if (act) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    if (col[p] == color || (zi && col[p] >= 0)) L.e[c[p]] = v[p];
+            }
+            Crew<W>::sync();
         }
     }
 };
-template <typename T, int NP>
+template <typename T, int NP, int W>
 __device__ __forceinline__ void co_smooth_nat(const Lv<T, 3> &L, int nu, int zero_init) {
-    NatCells<T, NP> c;
+    NatCells<T, NP, W> c;
     c.load(L);
     for (int s = 0; s < nu; ++s) c.sweep(L, zero_init && s == 0);
 }
 
-// Pre-smoothing and restriction, and prolongation and post-smoothing, of one level.  A level
-// here holds e and r in kCoarseLdsBytes, so at most 4096 cells in FP64 and 8192 in FP32.
-static_assert(kCoarseLdsBytes / (2 * sizeof(float)) <= 8 * kCoarseThreads, "cells per thread");
-template <typename T, typename X_>
+// Pre-smoothing and restriction, and prolongation and post-smoothing, of one level.  A red/black
+// level here holds e and r in kCoarseLdsBytes, so at most 4096 cells in FP64 and 8192 in FP32; a
+// plainly stored one has at most kCoarseNatCells where it takes more than that, and so 8192.
+static_assert(kCoarseLdsBytes / (2 * sizeof(float)) <= 8 * kCoarseThreads && kCoarseNatCells <= 4 * kCoarseThreads,
+              "cells per thread");
+template <typename T>
+__device__ __forceinline__ void co_nat(const Lv<T, 3> &L, int nu, int zero_init) {
+    const int n = L.nx * L.ny * L.nz;
+    if (n <= kCoarseThreads) co_smooth_nat<T, 1, 0>(L, nu, zero_init);
+    else if (n <= 2 * kCoarseThreads) co_smooth_nat<T, 2, 0>(L, nu, zero_init);
+    else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4, 0>(L, nu, zero_init);
+    else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8, 0>(L, nu, zero_init);
+}
+template <int W, typename T, typename X_>
 __device__ __forceinline__ void co_down(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
     if (L.rb) {
         const int n = (L.nx >> 1) * L.ny * L.nz;
-        if (n <= kCoarseThreads) co_pre_rb<T, 1>(L, C, X, nu);
-        else if (n <= 2 * kCoarseThreads) co_pre_rb<T, 2>(L, C, X, nu);
-        else if constexpr (sizeof(T) == 4) co_pre_rb<T, 4>(L, C, X, nu);
+        if (W || n <= kCoarseThreads) co_pre_rb<T, 1, W>(L, C, X, nu);
+        else if (n <= 2 * kCoarseThreads) co_pre_rb<T, 2, W>(L, C, X, nu);
+        else if constexpr (sizeof(T) == 4 && !W) co_pre_rb<T, 4, W>(L, C, X, nu);
         if (X.xy == 1) return;
+    } else if (W) {
+        co_smooth_nat<T, 1, W>(L, nu, 1);
     } else {
-        const int n = L.nx * L.ny * L.nz;
-        if (n <= kCoarseThreads) co_smooth_nat<T, 1>(L, nu, 1);
-        else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4>(L, nu, 1);
-        else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8>(L, nu, 1);
+        co_nat(L, nu, 1);
     }
     const int n = C.nx * C.ny * C.nz;
     const Split3 sp{fdiv_of(C.nx), fdiv_of(C.ny)};
-    for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
+    for (int c = threadIdx.x; c < n; c += Crew<W>::size) {
         int I0, J0, K0;
         split_c(c, sp, I0, J0, K0);
         restrict_cell(L, C, X, I0, J0, K0);
     }
-    __syncthreads();
+    Crew<W>::sync();
 }
-template <typename T, typename X_>
+template <int W, typename T, typename X_>
 __device__ __forceinline__ void co_up(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
     if (L.rb) {
         const int hx = L.nx >> 1;
         const int n = hx * L.ny * L.nz;
         T FX_AS(3) *eb = L.e + n;
         const Split3 sp{fdiv_of(hx), fdiv_of(L.ny)};
-        for (int q = threadIdx.x; q < n; q += kCoarseThreads) {
+        for (int q = threadIdx.x; q < n; q += Crew<W>::size) {
             int m, j, k;
             split_c(q, sp, m, j, k);
             const int i = 2 * m + ((1 + j + k) & 1);
@@ -2192,22 +2246,21 @@ __device__ __forceinline__ void co_up(const Lv<T, 3> &L, const Lv<T, 3> &C, cons
                         : X.xy == 2 ? prolong_value<2>(C, X, i, j, k) : prolong_value<0>(C, X, i, j, k);
             eb[q] += v;
         }
-        __syncthreads();
-        if (n <= kCoarseThreads) co_post_rb<T, 1>(L, nu);
-        else if (n <= 2 * kCoarseThreads) co_post_rb<T, 2>(L, nu);
-        else if constexpr (sizeof(T) == 4) co_post_rb<T, 4>(L, nu);
+        Crew<W>::sync();
+        if (W || n <= kCoarseThreads) co_post_rb<T, 1, W>(L, nu);
+        else if (n <= 2 * kCoarseThreads) co_post_rb<T, 2, W>(L, nu);
+        else if constexpr (sizeof(T) == 4 && !W) co_post_rb<T, 4, W>(L, nu);
     } else {
         const int n = L.nx * L.ny * L.nz;
         const Split3 sp{fdiv_of(L.nx), fdiv_of(L.ny)};
-        for (int c = threadIdx.x; c < n; c += kCoarseThreads) {
+        for (int c = threadIdx.x; c < n; c += Crew<W>::size) {
             int i, j, k;
             split_c(c, sp, i, j, k);
             prolong_cell(L, C, X, i, j, k);
         }
-        __syncthreads();
-        if (n <= kCoarseThreads) co_smooth_nat<T, 1>(L, nu, 0);
-        else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4>(L, nu, 0);
-        else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8>(L, nu, 0);
+        Crew<W>::sync();
+        if (W) co_smooth_nat<T, 1, W>(L, nu, 0);
+        else co_nat(L, nu, 0);
     }
 }
 
@@ -2221,6 +2274,11 @@ __device__ __forceinline__ double dpp_add(double v) {
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
     return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 __device__ __forceinline__ double wave_sum(double v) {
     v = dpp_add<0x111, 0xf>(v);                        // row_shr 1, 2, 4, 8
     v = dpp_add<0x112, 0xf>(v);
@@ -2228,21 +2286,32 @@ __device__ __forceinline__ double wave_sum(double v) {
     v = dpp_add<0x118, 0xf>(v);
     v = dpp_add<0x142, 0xa>(v);                        // row_bcast 15, 31
     v = dpp_add<0x143, 0xc>(v);
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    return lane_value(v, 63);
 }
 
-// Sum over the workgroup in a fixed order; every thread gets the total.  red holds one
-// partial per wave; the caller's next write to it comes after another barrier.
-__device__ __forceinline__ double block_total(double v, double FX_AS(3) *red) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+// Two sums over the workgroup in a fixed order; every thread gets the totals.  red holds a pair of
+// partials per wave (act: this wave has terms); the caller's next write to it comes after
+// another barrier.
+__device__ __forceinline__ void block_totals(double &x, double &y, double FX_AS(3) *red, bool act) {
+    constexpr int NW = kCoarseThreads / 64;
+    static_assert(NW == 16, "a partial per lane of a row of 16");
+    if (act) {
+        x = wave_sum(x);
+        y = wave_sum(y);
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+        red[wave] = act ? x : 0.0;
+        red[NW + wave] = act ? y : 0.0;
+    }
     __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < kCoarseThreads / 64; ++q) t += red[q];
-    return t;
+    double v = red[lane & (2 * NW - 1)];                   // row 0 the x partials, row 1 those of y
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    x = lane_value(v, 15);
+    y = lane_value(v, 31);
 }
 
 // Bottom solve on the coarsest level: conjugate gradients on the symmetric
@@ -2306,92 +2375,135 @@ __device__ void bottom_cg_wave(const Lv<T, 3> &B, int iters, double tol2) {
     }
 }
 
-// A thread per cell, NP cells each: x, r, the search direction's own value and the operator's
-// row stay in registers, the direction is shared through LDS (ps).  red, red2: two sets of partials,
-// so that a sum's partials are not overwritten while another wave still reads them.
+// A bottom level of at most 8 cells, solved directly by the first wave: lane 8 i + j holds the
+// matrix entry (i, j), every lane of row i the right-hand side; Gauss-Jordan without pivoting
+// (the matrix is symmetric positive definite), a step per cell.  Bound by the latency of its
+// steps, about 300 cycles each; the conjugate gradients took 2500 a step (22000 cycles of the
+// 16 x 16 x 20 stack's 63000 on its 8 cells).
+template <typename T>
+__device__ __forceinline__ void bottom_direct(const Lv<T, 3> &B) {
+    const int n = B.nx * B.ny * B.nz, plane = B.nx * B.ny;
+    const int lane = threadIdx.x, row = lane >> 3, col = lane & 7;
+    const bool on = row < n;
+    const int c = on ? row : 0;
+    const Split3 sp{fdiv_of(B.nx), fdiv_of(B.ny)};
+    int i, j, k;
+    split_c(c, sp, i, j, k);
+    const double cx = (double)B.cxy[k];
+    const double wx = B.nx > 1 ? cx : 0.0, wy = B.ny > 1 ? cx : 0.0;
+    const int base = c - i;
+    double a = 0.0;
+    a -= base + wrap_p(i, B.nx) == col ? wx : 0.0;
+    a -= base + wrap_m(i, B.nx) == col ? wx : 0.0;
+    a -= k * plane + wrap_p(j, B.ny) * B.nx + i == col ? wy : 0.0;
+    a -= k * plane + wrap_m(j, B.ny) * B.nx + i == col ? wy : 0.0;
+    a -= k > 0 && c - plane == col ? (double)B.czm[k] : 0.0;
+    a -= k < B.nz - 1 && c + plane == col ? (double)B.czp[k] : 0.0;
+    if (c == col) a += (double)diag_of(B, i, j, k);
+    if (!on) a = row == col ? 1.0 : 0.0;
+    const int ci = cidx(B, i, j, k);
+    double x = on ? (double)B.r[ci] : 0.0;
+    for (int p = 0; p < n; ++p) {
+        const double inv = rcp_newton(__shfl(a, 9 * p, 64));
+        const double ar = __shfl(a, 8 * p + col, 64) * inv, xr = __shfl(x, 8 * p, 64) * inv;
+        const double f = __shfl(a, 8 * row + p, 64);
+        a = row == p ? ar : __builtin_fma(-f, ar, a);
+        x = row == p ? xr : __builtin_fma(-f, xr, x);
+    }
+    if (on && col == 0) B.e[ci] = (T)x;
+}
+
+// A thread per cell, NP cells each; the vectors stay in registers, the residual is shared through
+// LDS (rs).  The recurrences are Chronopoulos and Gear's (1989): with w = A r, both inner
+// products of a step, (r, r) and (w, r), are summed together, so a step is one exchange of r
+// and one reduction, two barriers (about 1000 cycles; three exchanges and sums of 16 partials
+// in sequence took 2200).
 template <typename T, int NP>
-__device__ __forceinline__ void bottom_cg_block(const Lv<T, 3> &B, T FX_AS(3) *ps, double FX_AS(3) *red,
-                                                double FX_AS(3) *red2, int iters, double tol2) {
+__device__ __forceinline__ void bottom_cg_block(const Lv<T, 3> &B, T FX_AS(3) *rs, double FX_AS(3) *red, int iters,
+                                                double tol2) {
     const int n = B.nx * B.ny * B.nz, plane = B.nx * B.ny;
     const Split3 sp{fdiv_of(B.nx), fdiv_of(B.ny)};
-    double r[NP], x[NP], d[NP], p[NP], cx[NP], cy[NP], cm[NP], cp[NP];
+    double r[NP], x[NP], d[NP], p[NP], s[NP], cx[NP], cy[NP], cm[NP], cp[NP];
     int c[NP], ci[NP], ox[2][NP], oy[2][NP], oz[2][NP];
     bool on[NP];
-    double rr = 0.0;
+    const bool act = wave_first() < n;
+    if (act) {
 #pragma unroll
-    for (int u = 0; u < NP; ++u) {
-        const int cc = threadIdx.x + u * kCoarseThreads;
-        on[u] = cc < n;
-        c[u] = on[u] ? cc : 0;
-        int i, j, k;
-        split_c(c[u], sp, i, j, k);
-        ci[u] = cidx(B, i, j, k);
-        ox[0][u] = wrap_p(i, B.nx) - i;
-        ox[1][u] = wrap_m(i, B.nx) - i;
-        oy[0][u] = (wrap_p(j, B.ny) - j) * B.nx;
-        oy[1][u] = (wrap_m(j, B.ny) - j) * B.nx;
-        oz[0][u] = k > 0 ? -plane : 0;
-        oz[1][u] = k < B.nz - 1 ? plane : 0;
-        cx[u] = on[u] && B.nx > 1 ? (double)B.cxy[k] : 0.0;
-        cy[u] = on[u] && B.ny > 1 ? (double)B.cxy[k] : 0.0;
-        cm[u] = on[u] && k > 0 ? (double)B.czm[k] : 0.0;
-        cp[u] = on[u] && k < B.nz - 1 ? (double)B.czp[k] : 0.0;
-        d[u] = on[u] ? (double)diag_of(B, i, j, k) : 0.0;
-        r[u] = on[u] ? (double)B.r[ci[u]] : 0.0;
-        x[u] = 0.0;
-        p[u] = r[u];
-        rr += r[u] * r[u];
-        if (on[u]) ps[c[u]] = (T)p[u];
+        for (int u = 0; u < NP; ++u) {
+            const int cc = threadIdx.x + u * kCoarseThreads;
+            on[u] = cc < n;
+            c[u] = on[u] ? cc : 0;
+            int i, j, k;
+            split_c(c[u], sp, i, j, k);
+            ci[u] = cidx(B, i, j, k);
+            ox[0][u] = wrap_p(i, B.nx) - i;
+            ox[1][u] = wrap_m(i, B.nx) - i;
+            oy[0][u] = (wrap_p(j, B.ny) - j) * B.nx;
+            oy[1][u] = (wrap_m(j, B.ny) - j) * B.nx;
+            oz[0][u] = k > 0 ? -plane : 0;
+            oz[1][u] = k < B.nz - 1 ? plane : 0;
+            cx[u] = on[u] && B.nx > 1 ? (double)B.cxy[k] : 0.0;
+            cy[u] = on[u] && B.ny > 1 ? (double)B.cxy[k] : 0.0;
+            cm[u] = on[u] && k > 0 ? (double)B.czm[k] : 0.0;
+            cp[u] = on[u] && k < B.nz - 1 ? (double)B.czp[k] : 0.0;
+            d[u] = on[u] ? (double)diag_of(B, i, j, k) : 0.0;
+            r[u] = on[u] ? (double)B.r[ci[u]] : 0.0;
+            x[u] = p[u] = s[u] = 0.0;
+        }
     }
-    rr = block_total(rr, red);                         // its barrier also publishes ps
-    const double stop = tol2 * rr;
-    for (int it = 0; it < iters && rr > stop; ++it) {
-        double q[NP], pq = 0.0;
+    double g_old = 1.0, a_old = 1.0, stop = 0.0;
+    for (int it = 0; it <= iters; ++it) {
+        if (act) {
 #pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            const T FX_AS(3) *e = ps + c[u];
-            p[u] = on[u] ? (double)e[0] : 0.0;         // the direction as its neighbours see it
-            q[u] = d[u] * p[u] - cx[u] * ((double)e[ox[0][u]] + (double)e[ox[1][u]]) -
-                   cy[u] * ((double)e[oy[0][u]] + (double)e[oy[1][u]]) - cm[u] * (double)e[oz[0][u]] -
-                   cp[u] * (double)e[oz[1][u]];
-            pq += p[u] * q[u];
+            for (int u = 0; u < NP; ++u)
+                if (on[u]) rs[c[u]] = (T)r[u];
         }
-        pq = block_total(pq, red2);
-        if (!(pq > 0.0)) break;
-        const double alpha = rr / pq;
-        double rn = 0.0;
+        __syncthreads();
+        double w[NP], g = 0.0, h = 0.0;
+        if (act) {
 #pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            x[u] += alpha * p[u];
-            r[u] -= alpha * q[u];
-            rn += r[u] * r[u];
+            for (int u = 0; u < NP; ++u) {
+                const T FX_AS(3) *e = rs + c[u];
+                if (on[u]) r[u] = (double)e[0];            // the residual as its neighbours see it
+                w[u] = d[u] * r[u] - cx[u] * ((double)e[ox[0][u]] + (double)e[ox[1][u]]) -
+                       cy[u] * ((double)e[oy[0][u]] + (double)e[oy[1][u]]) - cm[u] * (double)e[oz[0][u]] -
+                       cp[u] * (double)e[oz[1][u]];
+                g += r[u] * r[u];
+                h += w[u] * r[u];
+            }
         }
-        rn = block_total(rn, red);
-        const double beta = rn / rr;
-        rr = rn;
+        block_totals(g, h, red, act);
+        if (it == 0) stop = tol2 * g;
+        if (!(g > stop) || it == iters) break;
+        const double beta = it ? g * rcp_newton(g_old) : 0.0;
+        const double den = it ? h - beta * g * rcp_newton(a_old) : h;
+        if (!(den > 0.0)) break;
+        const double alpha = g * rcp_newton(den);
+        g_old = g;
+        a_old = alpha;
+        if (act) {
+#pragma unroll
+            for (int u = 0; u < NP; ++u) {
+                p[u] = r[u] + beta * p[u];
+                s[u] = w[u] + beta * s[u];
+                x[u] += alpha * p[u];
+                r[u] -= alpha * s[u];
+            }
+        }
+    }
+    if (act) {
 #pragma unroll
         for (int u = 0; u < NP; ++u)
-            if (on[u]) ps[c[u]] = (T)(r[u] + beta * p[u]);
-        __syncthreads();
+            if (on[u]) B.e[ci[u]] = (T)x[u];
     }
-#pragma unroll
-    for (int u = 0; u < NP; ++u)
-        if (on[u]) B.e[ci[u]] = (T)x[u];
     __syncthreads();
 }
 
+// The bottom solve by the whole workgroup (n > 64) or by its first wave.
 template <typename T>
-__device__ __forceinline__ void bottom_cg(const Lv<T, 3> &B, T FX_AS(3) *p, double FX_AS(3) *red, double FX_AS(3) *red2,
-                                          int iters, double tol2) {
-    const int n = B.nx * B.ny * B.nz;
-    if (n <= 64) {
-        if (threadIdx.x < 64) bottom_cg_wave(B, iters, tol2);
-        __syncthreads();
-    } else if (n <= kCoarseThreads) {
-        bottom_cg_block<T, 1>(B, p, red, red2, iters, tol2);
-    } else {
-        bottom_cg_block<T, 2>(B, p, red, red2, iters, tol2);
-    }
+__device__ __forceinline__ void bottom_wave(const Lv<T, 3> &B, int iters, double tol2) {
+    if (B.nx * B.ny * B.nz <= 8) bottom_direct(B);
+    else bottom_cg_wave(B, iters, tol2);
 }
 
 // A block per instance: the V-cycle from level lc down to the coarsest with
@@ -2401,9 +2513,11 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(const Inst<T> *I, Ins
     extern __shared__ double lds_raw[];
     const Inst<T> &A = I[blockIdx.x];
     const GState *sta = asp<1>(S + blockIdx.x);
-    if (sta->done) return;
+    // read together, one exit test: see smooth_kernel
+    const int done = sta->done, light = sta->light, l0 = A.lc, nl = A.nlev - A.lc, qw = A.wave_lev;
+    const int nu1 = light ? 1 : A.nu1, nu2 = light ? 1 : A.nu2;
+    if ((done != 0) | (l0 < 0)) return;
     unsigned char FX_AS(3) *lds = asp<3>((unsigned char *)lds_raw);
-    const int l0 = A.lc, nl = A.nlev - A.lc;
     auto lvl = [&](int q) {
         const LevelArgs<T> &G = A.lv[l0 + q];
         Lv<T, 3> L;
@@ -2530,12 +2644,24 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(const Inst<T> *I, Ins
         }
     }
     __syncthreads();
-    const int light = sta->light;
-    const int nu1 = light ? 1 : A.nu1, nu2 = light ? 1 : A.nu2;
-    for (int q = 0; q < nl - 1; ++q) co_down(lvl(q), lvl(q + 1), xlds(q), nu1);
-    bottom_cg<T>(lvl(nl - 1), (T FX_AS(3) *)(lds + A.off_p), (double FX_AS(3) *)(lds + A.off_red),
-                 (double FX_AS(3) *)(lds + A.off_q), A.bottom_iters, A.bottom_tol2);
-    for (int q = nl - 2; q >= 0; --q) co_up(lvl(q), lvl(q + 1), xlds(q), nu2);
+    // levels qw.. and the bottom fit one wave (qw = nl: the bottom does not)
+    for (int q = 0; q < min(qw, nl - 1); ++q) co_down<0>(lvl(q), lvl(q + 1), xlds(q), nu1);
+    if (qw >= nl) {
+        const Lv<T, 3> B = lvl(nl - 1);
+        T FX_AS(3) *rs = (T FX_AS(3) *)(lds + A.off_p);
+        double FX_AS(3) *red = (double FX_AS(3) *)(lds + A.off_q);       // more than 64 cells: room for 32
+        if (B.nx * B.ny * B.nz <= kCoarseThreads) bottom_cg_block<T, 1>(B, rs, red, A.bottom_iters, A.bottom_tol2);
+        else bottom_cg_block<T, 2>(B, rs, red, A.bottom_iters, A.bottom_tol2);
+    } else {
+        if (threadIdx.x < 64) {
+            for (int q = qw; q < nl - 1; ++q) co_down<1>(lvl(q), lvl(q + 1), xlds(q), nu1);
+            bottom_wave<T>(lvl(nl - 1), A.bottom_iters, A.bottom_tol2);
+            Crew<1>::sync();
+            for (int q = nl - 2; q >= qw; --q) co_up<1>(lvl(q), lvl(q + 1), xlds(q), nu2);
+        }
+        __syncthreads();
+    }
+    for (int q = min(qw, nl - 1) - 1; q >= 0; --q) co_up<0>(lvl(q), lvl(q + 1), xlds(q), nu2);
     {
         const Lv<T, 1> G = gview(A.lv[l0]);
         const Lv<T, 3> L0 = lvl(0);

@@ -237,7 +237,9 @@ void build_plan(const fx_stack_desc *d, Plan *p) {
         tail += (2 * L.ncell() + L.nsig() + 4 * L.nz) * w + 64;
         if (l == nlev - 1) tail += 2 * L.ncell() * w + 16 * sizeof(double) + 64;   // bottom-solve vectors
         else tail += 3 * (L.nz + p->lv[l + 1].nz) * sizeof(int) + 2 * L.nz * w + 48;  // transfer tables
-        if (tail > (size_t)kCoarseLdsBytes) break;
+        // (the coarsest level alone keeps to kCoarseLdsBytes)
+        const bool nat = !p->lv[l].rb && L.ncell() <= (size_t)kCoarseNatCells && l < nlev - 1;
+        if (tail > (size_t)(nat ? kCoarseNatLds : kCoarseLdsBytes)) break;
         p->lc = l;
     }
     int xy_pow = 0;
@@ -800,6 +802,14 @@ Inst<T> make_inst(const Engine *e, int i) {
         a.bottom_tol2 = rt * rt;
     }
     a.lds_bytes = coarse_layout<T>(p, &a);
+    // levels whose colour (red/black) or cells (plain) fit one wave, with all below them
+    const int nl = a.nlev - a.lc;
+    a.wave_lev = nl;
+    for (int q = nl - 1; q >= 0; --q) {
+        const HostLevel &H = p.lv[p.lc + q];
+        if ((q < nl - 1 && H.rb ? H.ncell() / 2 : H.ncell()) > 64) break;
+        a.wave_lev = q;
+    }
     return a;
 }
 
@@ -867,7 +877,9 @@ fx_status upload_all(Engine *e) {
         for (size_t l = 0; l < p.lv.size(); ++l) put_level(e, p.lv[l], D[l]);
         host[i] = make_inst<T>(e, i);
         h.lds = host[i].lds_bytes;
-        if (h.lds > kCoarseLdsBytes) return fail(FX_EINVAL, "coarse levels need %d bytes of LDS", h.lds);
+        const bool alone = p.lc == (int)p.lv.size() - 1;
+        if (h.lds > (alone ? kCoarseLdsBytes : kCoarseNatLds))
+            return fail(FX_EINVAL, "coarse levels need %d bytes of LDS", h.lds);
         e->lds_max = std::max(e->lds_max, h.lds);
     }
     put_table(e, e->inst_dev, host.data(), (size_t)e->n * sizeof(Inst<T>));
