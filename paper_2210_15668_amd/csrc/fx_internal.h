@@ -78,6 +78,19 @@ __host__ __device__ constexpr size_t tb_lds_bytes(int nz, int nzc, size_t w) {
             (size_t)nzc * (kTbW / 2 + 2) * (kTbW / 2 + 2) + nz) * w;
 }
 static_assert(tb_lds_bytes(kTbMaxNz, kTbMaxNz / 2, sizeof(double)) <= 160 * 1024, "a workgroup's LDS");
+// temporal blocking marching in z (k_pre_zm / k_post_zm)
+constexpr int kZmT = 32;                   // tile edge (cells)
+constexpr int kZmH = 4;                    // ring and halo planes
+constexpr int kZmMaxZl = 96;               // planes per chunk
+// planes in a march's tables: the chunk, its halo, and up to 3 steps of the last group of four
+__host__ __device__ constexpr int kZmTab(int zl) { return zl + 2 * kZmH + 4; }
+__host__ __device__ constexpr size_t zm_lds_bytes(int zl, int post, size_t w) {
+    const size_t cells = (size_t)(kZmT + 2 * kZmH) / 2 * (kZmT + 2 * kZmH), plane = cells + 48, cw = (kZmT + 2 * kZmH) / 2 + 2;
+    return post ? (8 * plane + 4 * cw * cw + 8 * cells + 8 * (size_t)kZmTab(zl)) * w
+                : (14 * plane + 8 * cells + 5 * (size_t)kZmTab(zl) + 1) * w + (size_t)kZmTab(zl) * sizeof(double);
+}
+static_assert(zm_lds_bytes(kZmMaxZl, 0, sizeof(double)) <= 160 * 1024 && zm_lds_bytes(kZmMaxZl, 1, sizeof(double)) <= 160 * 1024,
+              "a workgroup's LDS");
 constexpr int kQvBlocks = 8;      // blocks per instance of the interface-plane reductions
 constexpr int kRecSteps = 1024;   // recorded steps per instance held on the device
 
@@ -261,6 +274,9 @@ template <typename T> void launch_coarse(const Inst<T> *I, InstState *S, int nin
 // tile; nz, nzc: the most planes of an instance on this level and the next
 template <typename T> void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, hipStream_t st);
 template <typename T> void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, int nzc, hipStream_t st);
+// the same on a level of any size, in z-chunks of zl planes (a multiple of 4)
+template <typename T> void launch_pre_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st);
+template <typename T> void launch_post_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st);
 template <typename T> void launch_head(const Inst<T> *I, InstState *S, int ninst, int advance, hipStream_t st);
 template <typename T> void launch_run_setup(const Inst<T> *I, int ninst, int nsteps, int has_sched, double dt,
                                             int first, hipStream_t st);

@@ -1930,6 +1930,557 @@ __global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w
     }
 }
 
+// ------------------------------------------- temporal blocking, marching in z
+// The same two launches on levels too large for boxes of whole columns: a block owns a
+// kZmT x kZmT tile of a chunk of planes, with a ring of kZmH cells in x and y and kZmH planes at
+// either end, and marches up in z with all half-sweeps in flight: in step k the first one works on
+// plane k, each later stage one plane below the stage before it, and the last (the residual,
+// or the finished values) on plane k - 4.  A thread owns a storage pair (a red and a black
+// cell of one row) through the march, so a cell's z neighbours and its x neighbour in the pair
+// are the thread's own recent values of the other colour, in registers; the other x neighbour
+// and the two y neighbours come from the stage's plane in LDS, double-buffered, one barrier
+// per step.  Right-hand sides and sigma are loaded two planes ahead, once per block.
+// Expressions and operands are those of the half-sweep launches (nb6, gs_value's product,
+// res_value, lint_xy, lint_z, the restriction's sums in order): the same bits.  Invalid values
+// at the ring and beyond a chunk's ends move inwards one cell per stage and never reach the
+// tile.  A light cycle passes the last two half-sweeps' values through.
+//
+// What bounds it: on 256 x 256 x 120 cells the half-sweep launches and transfers of a cycle read
+// and write 1.2 GB (231 us); here r, sigma, phi and the black values are read once per launch
+// (0.4 GB), and the steps' instructions over 1.56 x (zl + 8) / zl cells take over: 77 + 82 us
+// (FP32 65 + 60, launches 138; 32 instances of 64 x 64 x 24: 29 + 35, launches 141).  Tiles of
+// 32 x 16 with two blocks per compute unit measured 82 + 87, 68 + 64 and 27 + 34.
+constexpr int kZmThreads = 832;               // 800 pairs of the box, whole waves
+constexpr int kZmP = (kZmT + 2 * kZmH) / 2;   // pairs per box row
+constexpr int kZmN = kZmP * (kZmT + 2 * kZmH);
+constexpr int kZmPad = 24;                    // LDS neighbours of the box's edge cells stay inside
+constexpr int kZmA = kZmN + 2 * kZmPad;       // one stage's plane
+constexpr int kZmCW = kZmP + 2;               // coarse columns and rows under a box, with neighbours
+static_assert(kZmThreads % 64 == 0 && kZmThreads >= kZmN && kZmPad > kZmP, "box");
+
+__device__ __forceinline__ float uniform_value(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ double uniform_value(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <int V> using ic = std::integral_constant<int, V>;
+
+__device__ __forceinline__ int uniform_value(int v) {
+    // as asm: the builtin is dropped where the compiler sees the value to be uniform, and what
+    // is formed from it stays in vector registers (the nops keep a scalar use at its distance)
+    int o;
+    asm volatile("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 4" : "=s"(o) : "v"(v));
+    return o;
+}
+// A level whose extents are known to be the same in all lanes: plane addresses stay scalar.
+template <typename A>
+__device__ __forceinline__ auto zm_view(const A &a) {
+    auto L = gview(a);
+    L.nx = uniform_value(L.nx);
+    L.ny = uniform_value(L.ny);
+    L.nz = uniform_value(L.nz);
+    L.sig_lo = uniform_value(L.sig_lo);
+    L.sig_hi = uniform_value(L.sig_hi);
+    return L;
+}
+// A loaded value in a register of its own: the next load into the source's register may follow
+// at once, where the compiler would else load elsewhere and move that value, waiting for it.
+__device__ __forceinline__ float zm_take(float v) {
+    float o;
+    asm("v_mov_b32 %0, %1" : "=&v"(o) : "v"(v));
+    return o;
+}
+__device__ __forceinline__ double zm_take(double v) {
+    double o;
+    asm("v_mov_b64 %0, %1" : "=&v"(o) : "v"(v));
+    return o;
+}
+__device__ __forceinline__ dpair zm_take(dpair v) { return dpair{zm_take(v.x), zm_take(v.y)}; }
+struct ZmBlk {
+    int tx, ty, z0, z1, k0;                // tile, planes [z0, z1) of the chunk, first plane of the march
+    int q0;                                // global pair index in a plane
+    int lp, x[2];                          // LDS index; of the red cell's other x neighbour on even / odd planes
+    int row, m, gi2, gj;                   // box row and pair; wrapped pair column and row
+    bool own;                              // pair of the tile and of the grid
+};
+template <typename V>
+__device__ __forceinline__ ZmBlk zm_block(const V &L, int t, int zl) {
+    ZmBlk c;
+    const int nzc = (L.nz + zl - 1) / zl, ntx = (L.nx + kZmT - 1) / kZmT;
+    // the chunks of a tile, then the tiles of a row, on one XCD (divisions leave the scalar unit)
+    const int q = t / nzc, zc = uniform_value(t - q * nzc), qy = q / ntx;
+    c.tx = uniform_value(q - qy * ntx);
+    c.ty = uniform_value(qy);
+    c.z0 = zc * zl;
+    c.z1 = min(c.z0 + zl, L.nz);
+    c.k0 = max(c.z0 - kZmH, 0);
+    const int tid = min((int)threadIdx.x, kZmN - 1);
+    c.row = tid / kZmP;
+    c.m = tid - c.row * kZmP;
+    const int hx = L.nx >> 1;
+    int gm = c.tx * (kZmT / 2) - kZmH / 2 + c.m, gj = c.ty * kZmT - kZmH + c.row;
+    const bool in = c.m >= kZmH / 2 && c.m < kZmH / 2 + kZmT / 2 && c.row >= kZmH && c.row < kZmH + kZmT;
+    c.own = in && gm < hx && gj < L.ny && (int)threadIdx.x < kZmN;
+    gm = (gm % hx + hx) % hx;              // extents may be smaller than the box
+    gj = (gj % L.ny + L.ny) % L.ny;
+    c.gi2 = gm;
+    c.gj = gj;
+    c.q0 = gj * hx + gm;
+    c.lp = kZmPad + c.row * kZmP + c.m;
+    c.x[0] = c.lp + ((c.row & 1) ? 1 : -1);    // ny even: the box row's parity is the grid row's
+    c.x[1] = c.lp + ((c.row & 1) ? -1 : 1);
+    return c;
+}
+
+// Tables in LDS of the march's planes (zeros past the top, so that what is formed there is 0):
+// reciprocal and plain diagonal, coefficients.
+template <typename T>
+struct ZmTab {
+    T FX_AS(3) *p;
+    int k0, n;
+    __device__ __forceinline__ void fill(const Lv<T, 1> &L) const {
+        for (int q = threadIdx.x; q < n; q += kZmThreads) {
+            const int k = k0 + q;
+            const bool in = k < L.nz;
+            const T dg = in ? L.dg[k] : T(0);
+            p[5 * q] = in ? T(1) / dg : T(0);
+            p[5 * q + 1] = dg;
+            p[5 * q + 2] = in ? L.cxy[k] : T(0);
+            p[5 * q + 3] = in && k > 0 ? L.czm[k] : T(0);
+            p[5 * q + 4] = in && k < L.nz - 1 ? L.czp[k] : T(0);
+        }
+    }
+    __device__ __forceinline__ T at(int k, int q) const { return uniform_value((T)p[5 * (max(k, k0) - k0) + q]); }
+};
+
+// Reciprocal diagonals: uniform over a plane without sigma; in a chunk with sigma, the
+// thread's own of the last four planes in LDS (each reads back what it wrote: no barrier).
+template <typename T, int SIG>
+struct ZmIv {
+    T FX_AS(3) *p;                         // slots [colour][plane mod 4]
+    const T (&uni)[5];                     // the uniform values of planes k .. k - 4
+    __device__ __forceinline__ T get(const Lv<T, 1> &L, int col, int k, int d) const {
+        if (!SIG) return uni[d];
+        return p[(4 * col + ((k - d) & 3)) * kZmN];
+    }
+    __device__ __forceinline__ void put(int col, int k, T v) const { p[(4 * col + (k & 3)) * kZmN] = v; }
+};
+
+// A value of a stage's plane: other colour's neighbours in LDS (x: the x neighbour outside the
+// pair), the pair's own cell and the z neighbours in registers.
+template <typename T>
+__device__ __forceinline__ T zm_nb(const T FX_AS(3) *pl, const ZmBlk &c, int x, T cx, T cm, T cp, T pair, T lo, T hi) {
+    return nb6(cx, cx, cm, cp, pair, pl[x], pl[c.lp + kZmP], pl[c.lp - kZmP], lo, hi);
+}
+// gs_value with the reciprocal at hand
+template <typename T>
+__device__ __forceinline__ T zm_gs(T rhs, T iv) {
+#pragma clang fp contract(off)
+    return rhs * iv;
+}
+// The stages' planes below the first one: finite values, which zero coefficients then drop.
+template <typename T>
+__device__ __forceinline__ void zm_clear(T FX_AS(3) *lds, int n) {
+    for (int u = threadIdx.x; u < n; u += kZmThreads) lds[u] = T(0);
+}
+template <int N, typename T>
+__device__ __forceinline__ void zm_push(T (&h)[N], T v) {
+#pragma unroll
+    for (int q = N - 1; q > 0; --q) h[q] = h[q - 1];
+    h[0] = v;
+}
+
+// Keeps the scheduler from gathering the loads of all stages, which FP64 has no registers for.
+template <typename T, int SIG>
+__device__ __forceinline__ void zm_fence() {
+    if (sizeof(T) == 8 && SIG) __builtin_amdgcn_sched_barrier(0);
+}
+
+// The operands of a plane, loaded two steps ahead; o, os: the pair's cell index on the plane and
+// in sigma's planes (past the top: the last plane's; without sigma: the nearest's, unused).
+// The indices go up plane by plane: a product per load cost more than the addition.
+template <typename V>
+__device__ __forceinline__ int zm_next(const V &L, int k, int plane) { return k + 1 < L.nz ? plane : 0; }
+template <typename V>
+__device__ __forceinline__ int zm_next_sig(const V &L, int k, int plane) {
+    return k + 1 > L.sig_lo && k + 1 < L.sig_hi ? plane : 0;
+}
+template <typename V>
+__device__ __forceinline__ int zm_first_sig(const V &L, int k, int plane) {
+    return max(0, min(k, L.sig_hi - 1) - L.sig_lo) * plane;
+}
+template <typename T>
+struct ZmIn {
+    T r0, r1, s0, s1;
+    template <int SIG>
+    __device__ __forceinline__ ZmIn take() const {
+        return {zm_take(r0), zm_take(r1), SIG ? zm_take(s0) : T(0), SIG ? zm_take(s1) : T(0)};
+    }
+    template <int SIG>
+    __device__ __forceinline__ void load(const Lv<T, 1> &L, int o, int os, int half, int half_s) {
+        r0 = L.r[o];
+        r1 = L.r[half + o];
+        s0 = s1 = T(0);
+        if (SIG) {
+            s0 = L.sig[os];
+            s1 = L.sig[half_s + os];
+        }
+    }
+};
+// The march, in pairs of steps; sigma's code only in the chunks whose planes meet sigma.
+template <typename V>
+__device__ __forceinline__ bool zm_sig(const V &L, int k0, int k1) {
+    return k0 < L.sig_hi && k1 > L.sig_lo && L.sig_hi > L.sig_lo;
+}
+template <typename V, typename S>
+__device__ __forceinline__ void zm_march(const V &L, int k0, int k1, S &&step) {
+    if (zm_sig(L, k0, k1)) {
+#pragma unroll 1
+        for (int k = k0; k < k1; k += 2) {
+            step(k, 0, ic<1>());
+            step(k + 1, 1, ic<1>());
+        }
+    } else {
+#pragma unroll 1
+        for (int k = k0; k < k1; k += 2) {
+            step(k, 0, ic<0>());
+            step(k + 1, 1, ic<0>());
+        }
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kZmThreads) void k_pre_zm(const Inst<T> *I, Work w, int level, int nu, int zl) {
+    extern __shared__ double tb_raw[];
+    const Blk b = find_block(w);
+    const Inst<T> &a = I[b.inst];
+    const GState *st = wstate(w, b.inst);
+    const int done = st->done, light = st->light;
+    if (!b.ok | (done != 0) | (level < 0)) return;  // one exit test: see smooth_kernel
+    const bool two = nu > 1 && !light;              // the second sweep is made
+    const Lv<T, 1> L = zm_view(a.lv[level]), C = gview(a.lv[level + 1]);
+    const Xv<T> X = xview(a.xf[level]);
+    const ZmBlk c = zm_block(L, b.t, zl);
+    const int k1 = c.z1 + kZmH + 1;                 // the last plane's odd rows follow a step later
+    const int nz = L.nz, plane = (L.nx >> 1) * L.ny, half = plane * nz;
+    T FX_AS(1) *ealt = asp<1>(a.lv[level].ealt);
+    // LDS: double-buffered planes of the four half-sweeps, the residuals and the pair's sigmas
+    T FX_AS(3) *lds = asp<3>((T *)tb_raw);
+    auto buf = [&](int stage, int par) { return lds + (2 * stage + par) * kZmA; };
+    T FX_AS(3) *ivp = lds + 14 * kZmA + c.lp - kZmPad;
+    const ZmTab<T> tab{lds + 14 * kZmA + 8 * kZmN, c.k0, kZmTab(zl)};
+    double FX_AS(3) *wzt = (double FX_AS(3) *)(tab.p + ((5 * kZmTab(zl) + 1) & ~1));
+    zm_clear(lds, 14 * kZmA);
+    tab.fill(L);
+    for (int q = threadIdx.x; q < kZmTab(zl); q += kZmThreads) {
+        const int k = c.k0 + q;
+        wzt[q] = k < nz ? (double)X.fthick[k] / (double)X.cthick[k >> 1] : 0.0;
+    }
+    auto wz_of = [&](int k) { return uniform_value((double)wzt[max(k - c.k0, 0)]); };
+    T rr[5] = {}, rb[4] = {}, a0[3] = {}, b0[3] = {}, a1[3] = {}, b1[3] = {};
+    T cx[5] = {}, cm[5] = {}, cp[5] = {}, idg[5] = {};
+    T s4 = T(0);                                           // red sigma of the next residual plane
+    double sr = 0.0, ss = 0.0;
+    ZmIn<T> in[2];
+    // cell indices of the planes loaded next: k + 2 of a step
+    const int half_s = plane * (L.sig_hi - L.sig_lo);
+    int o = c.k0 * plane + c.q0, os = zm_first_sig(L, c.k0, plane) + c.q0;
+    auto advance = [&](int k) {
+        o += zm_next(L, k, plane);
+        os += zm_next_sig(L, k, plane);
+    };
+    int os4 = zm_first_sig(L, c.k0 - 3, plane) + c.q0;
+    const bool any_sig = zm_sig(L, c.k0, k1);
+    for (int q = 0; q < 2; ++q) {
+        if (any_sig) in[q].template load<1>(L, o, os, half, half_s);
+        else in[q].template load<0>(L, o, os, half, half_s);
+        advance(c.k0 + q);
+    }
+    // the coarse column of this thread's row and the one below it: even rows hold its sums
+    const int gI = c.gi2, gJ = c.gj >> 1;
+    const bool own_c = c.own && !(c.row & 1);
+    // the loads above are waited for here: the march's own waits then count its own loads
+    __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0)
+    __syncthreads();                                       // tables
+    auto step = [&](int k, int cur, auto sig_) {
+        constexpr int SIG = decltype(sig_)::value;
+        const int prv = cur ^ 1;                           // k0 is even: cur is the plane's parity
+        // waits are in the order of issue: what is needed soonest is loaded first
+        const T s4c = SIG ? zm_take(s4) : T(0);
+        const ZmIn<T> v = in[cur].template take<SIG>();
+        if (SIG) {
+            s4 = L.sig[os4];
+            os4 += zm_next_sig(L, k - 3, plane);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        in[cur].template load<SIG>(L, o, os, half, half_s);
+        advance(k + 2);
+        zm_push(idg, tab.at(k, 0));
+        zm_push(cx, tab.at(k, 2));
+        zm_push(cm, tab.at(k, 3));
+        zm_push(cp, tab.at(k, 4));
+        zm_push(rr, v.r0);
+        zm_push(rb, v.r1);
+        const ZmIv<T, SIG> iv{ivp, idg};
+        if (SIG) {
+            T v0 = idg[0], v1 = idg[0];
+            if (has_sig(L, k)) {
+                const T dg = tab.at(k, 1);
+                v0 = T(1) / (dg + v.s0);
+                v1 = T(1) / (dg + v.s1);
+            }
+            iv.put(0, k, v0);
+            iv.put(1, k, v1);
+            if (k == c.k0) {
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {              // planes below the march
+                    iv.put(0, k - q, T(0));
+                    iv.put(1, k - q, T(0));
+                }
+            }
+        }
+        // red, plane k, from a zero start
+        zm_push(a0, zm_gs(rr[0], iv.get(L, 0, k, 0)));
+        buf(0, cur)[c.lp] = a0[0];
+        zm_fence<T, SIG>();
+        // black, plane k - 1
+        zm_push(b0, zm_gs(rb[1] + zm_nb(buf(0, prv), c, c.x[cur], cx[1], cm[1], cp[1], a0[1], a0[2], a0[0]), iv.get(L, 1, k, 1)));
+        buf(1, cur)[c.lp] = b0[0];
+        zm_fence<T, SIG>();
+        // red, plane k - 2, and black, plane k - 3: a light cycle passes the first sweep's values through
+        const T a1n = zm_gs(rr[2] + zm_nb(buf(1, prv), c, c.x[cur], cx[2], cm[2], cp[2], b0[1], b0[2], b0[0]), iv.get(L, 0, k, 2));
+        zm_push(a1, two ? a1n : a0[2]);
+        buf(2, cur)[c.lp] = a1[0];
+        zm_fence<T, SIG>();
+        const T b1n = zm_gs(rb[3] + zm_nb(buf(2, prv), c, c.x[cur], cx[3], cm[3], cp[3], a1[1], a1[2], a1[0]), iv.get(L, 1, k, 3));
+        zm_push(b1, two ? b1n : b0[2]);
+        buf(3, cur)[c.lp] = b1[0];
+        zm_fence<T, SIG>();
+        // red residual, plane k - 4, and the restriction's sums: the odd row's last
+        T d4 = tab.at(k - 4, 1);
+        if (SIG) d4 = has_sig(L, k - 4) ? d4 + s4c : d4;
+        const T res = res_value(rr[4], d4, a1[2], zm_nb(buf(3, prv), c, c.x[cur], cx[4], cm[4], cp[4], b1[1], b1[2], b1[0]));
+        const int p = k - 5;
+        const double sp = fmad(wz_of(p), (double)buf(4, prv)[c.lp + kZmP], sr);
+        sr = fmad(wz_of(k - 4), (double)res, cur ? sp : 0.0);
+        buf(4, cur)[c.lp] = res;
+        if (c.own && k - 3 >= c.z0 && k - 3 < c.z1) ealt[(k - 3) * plane + c.q0] = b1[0];
+        if ((!cur || p == nz - 1) && own_c && p >= c.z0 && p < c.z1) C.r[cidx(C, gI, gJ, p >> 1)] = (T)(sp * 0.25);
+        if (SIG) {
+            // sigma of plane k - 1's odd row, then of plane k: the pair's cells in x order
+            if (has_sig(L, k - 1)) {
+                const double wz = wz_of(k - 1);
+                ss = fmad(wz, (double)buf(5, prv)[c.lp + kZmP], ss);
+                ss = fmad(wz, (double)buf(6, prv)[c.lp + kZmP], ss);
+                if ((!cur || !has_sig(L, k)) && own_c && k - 1 >= c.z0 && k - 1 < c.z1)
+                    C.sig[sidx(C, gI, gJ, (k - 1) >> 1)] = (T)(ss * 0.25);
+            }
+            if (has_sig(L, k)) {
+                const bool sw = ((c.row + cur) & 1) != 0;  // the black cell comes first
+                const T sa = sw ? v.s1 : v.s0, sb = sw ? v.s0 : v.s1;
+                const double wz = wz_of(k);
+                ss = fmad(wz, (double)sa, cur && has_sig(L, k - 1) ? ss : 0.0);
+                ss = fmad(wz, (double)sb, ss);
+                buf(5, cur)[c.lp] = sa;
+                buf(6, cur)[c.lp] = sb;
+            }
+        }
+        __syncthreads();
+    };
+    zm_march(L, c.k0, k1, step);
+}
+
+template <typename T, int FINEST>
+__global__ __launch_bounds__(kZmThreads) void k_post_zm(const Inst<T> *I, Work w, int level, int nu, int zl) {
+    extern __shared__ double tb_raw[];
+    const Blk b = find_block(w);
+    const Inst<T> &a = I[b.inst];
+    const GState *st = wstate(w, b.inst);
+    const int done = st->done, light = st->light;
+    if (!b.ok | (done != 0) | (level < 0)) return;  // one exit test: see smooth_kernel
+    const bool two = nu > 1 && !light;              // the second sweep is made
+    const Lv<T, 1> L = zm_view(a.lv[level]), C = gview(a.lv[level + 1]);
+    const Xv<T> X = xview(a.xf[level]);
+    const ZmBlk c = zm_block(L, b.t, zl);
+    const int k1 = c.z1 + kZmH;
+    const int nz = L.nz, plane = (L.nx >> 1) * L.ny, half = plane * nz;
+    const T FX_AS(1) *ealt = asp<1>(a.lv[level].ealt);
+    // LDS: double-buffered planes of the corrected black values and three half-sweeps; a ring of
+    // four coarse planes; tables
+    T FX_AS(3) *lds = asp<3>((T *)tb_raw);
+    auto buf = [&](int stage, int par) { return lds + (2 * stage + par) * kZmA; };
+    const int FX_AS(1) *pflags = asp<1>(a.pflags);
+    T FX_AS(3) *cbuf = lds + 8 * kZmA;
+    T FX_AS(3) *ivp = cbuf + 4 * kZmCW * kZmCW + c.lp - kZmPad;
+    const ZmTab<T> tab{cbuf + 4 * kZmCW * kZmCW + 8 * kZmN, c.k0, kZmTab(zl)};
+    T FX_AS(3) *wt = tab.p + 5 * kZmTab(zl);               // z weights of the parent and the neighbour plane, clipped planes
+    zm_clear(lds, 8 * kZmA);
+    tab.fill(L);
+    for (int q = threadIdx.x; q < kZmTab(zl); q += kZmThreads) {
+        const int k = c.k0 + q;
+        wt[3 * q] = k < nz ? X.pwa[k] : T(0);
+        wt[3 * q + 1] = k < nz && X.pkb[k] >= 0 ? X.pwb[k] : T(0);
+        if (FINEST) wt[3 * q + 2] = k < nz && (pflags[k] & PF_SC) ? T(1) : T(0);
+    }
+    // coarse planes: one value per thread
+    const int cq = min((int)threadIdx.x, kZmCW * kZmCW - 1), cj = cq / kZmCW, ci = cq - cj * kZmCW;
+    int CI = c.tx * (kZmT / 2) - kZmH / 2 - 1 + ci, CJ = c.ty * (kZmT / 2) - kZmH / 2 - 1 + cj;
+    CI = (CI % C.nx + C.nx) % C.nx;
+    CJ = (CJ % C.ny + C.ny) % C.ny;
+    auto cload = [&](int K) { return C.e[cidx(C, CI, CJ, max(0, min(K, C.nz - 1)))]; };
+    auto cstore = [&](int K, T v) {
+        if (threadIdx.x < kZmCW * kZmCW) cbuf[(K & 3) * (kZmCW * kZmCW) + threadIdx.x] = v;
+    };
+    const int K0 = c.k0 >> 1;
+    {
+        const T v0 = cload(K0 - 1), v1 = cload(K0), v2 = cload(K0 + 1);
+        cstore(K0 - 1, v0);
+        cstore(K0, v1);
+        cstore(K0 + 1, v2);
+    }
+    T cnext = cload(K0 + 2);
+    // the thread's coarse operands: its column, the x neighbour on either side, the y neighbour's row
+    const int co = (1 + (c.row >> 1)) * kZmCW + 1 + c.m, cy = (c.row & 1) ? kZmCW : -kZmCW;
+    const T wx[2] = {T(0.75), T(0.25)}, wy[2] = {T(0.75), T(0.25)};
+    T wgt[2][2];
+#pragma unroll
+    for (int yy = 0; yy < 2; ++yy)
+#pragma unroll
+        for (int xx = 0; xx < 2; ++xx) wgt[yy][xx] = wx[xx] * wy[yy];
+    auto lateral = [&](int K, int dx) {
+        const T FX_AS(3) *p = cbuf + (K & 3) * (kZmCW * kZmCW) + co;
+        T v[2][2];
+        v[0][0] = p[0];
+        v[0][1] = p[dx];
+        v[1][0] = p[cy];
+        v[1][1] = p[cy + dx];
+        return lint_xy<2, 2>(wgt, v);
+    };
+    T rr[4] = {}, rb[5] = {}, e0[3] = {}, a0[3] = {}, b0[3] = {}, a1[3] = {};
+    T cx[5] = {}, cm[5] = {}, cp[5] = {}, idg[5] = {};
+    ZmIn<T> in[2];
+    T eb[2];
+    // cell indices of the planes loaded next: k + 2 of a step
+    const int half_s = plane * (L.sig_hi - L.sig_lo);
+    int o = c.k0 * plane + c.q0, os = zm_first_sig(L, c.k0, plane) + c.q0;
+    auto advance = [&](int k) {
+        o += zm_next(L, k, plane);
+        os += zm_next_sig(L, k, plane);
+    };
+    const bool any_sig = zm_sig(L, c.k0, k1);
+    for (int q = 0; q < 2; ++q) {
+        if (any_sig) in[q].template load<1>(L, o, os, half, half_s);
+        else in[q].template load<0>(L, o, os, half, half_s);
+        eb[q] = ealt[o];
+        advance(c.k0 + q);
+    }
+    const size_t off = (size_t)a.kb * a.nx * a.ny;
+    const double FX_AS(1) *phi_in = nullptr;
+    double FX_AS(1) *phi_out = nullptr;
+    const size_t nxy = (size_t)L.nx * L.ny;
+    const double dmax = a.dmax;
+    dpair ph = {};                                         // phi of the plane that is finished next
+    if (FINEST) {
+        phi_in = asp<1>(a.phi[cyc_src(st)]) + off + max(c.k0 - 3, 0) * nxy + 2 * c.q0;
+        phi_out = asp<1>(a.phi[cyc_dst(st)]) + off + 2 * c.q0;
+    }
+    // the loads above are waited for here: the march's own waits then count its own loads
+    __builtin_amdgcn_s_waitcnt(0x0f70);                    // vmcnt(0)
+    __syncthreads();                                       // tables, coarse planes
+    auto step = [&](int k, int cur, auto sig_) {
+        constexpr int SIG = decltype(sig_)::value;
+        const int prv = cur ^ 1;                           // k0 is even: cur is the plane's parity
+        // waits are in the order of issue: what is needed soonest is loaded first
+        const dpair phk = zm_take(ph);
+        const ZmIn<T> v = in[cur].template take<SIG>();
+        const T ebk = zm_take(eb[cur]);
+        if (FINEST) {
+            ph = *(const dpair FX_AS(1) *)phi_in;
+            phi_in += k >= 3 && k - 2 < nz ? nxy : 0;      // the plane finished in the step after the next
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        in[cur].template load<SIG>(L, o, os, half, half_s);
+        eb[cur] = ealt[o];
+        advance(k + 2);
+        zm_push(idg, tab.at(k, 0));
+        zm_push(cx, tab.at(k, 2));
+        zm_push(cm, tab.at(k, 3));
+        zm_push(cp, tab.at(k, 4));
+        zm_push(rr, v.r0);
+        zm_push(rb, v.r1);
+        const ZmIv<T, SIG> iv{ivp, idg};
+        const T iv4 = iv.get(L, 1, k, 4);                  // ahead of its slot's next value
+        if (SIG) {
+            T v0 = idg[0], v1 = idg[0];
+            if (has_sig(L, k)) {
+                const T dg = tab.at(k, 1);
+                v0 = T(1) / (dg + v.s0);
+                v1 = T(1) / (dg + v.s1);
+            }
+            iv.put(0, k, v0);
+            iv.put(1, k, v1);
+            if (k == c.k0) {
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {              // planes below the march
+                    iv.put(0, k - q, T(0));
+                    iv.put(1, k - q, T(0));
+                }
+            }
+        }
+        // corrected black value, plane k: the black cell is at 2m + (1 + row + k) % 2
+        {
+            const int K = k >> 1, Kn = cur ? K + 1 : K - 1;
+            const int dx = ((c.row + cur) & 1) ? -1 : 1;
+            const T wa = uniform_value((T)wt[3 * (k - c.k0)]), wb = uniform_value((T)wt[3 * (k - c.k0) + 1]);
+            zm_push(e0, ebk + lint_z(wa, lateral(K, dx), wb, lateral(Kn, dx)));
+        }
+        buf(0, cur)[c.lp] = e0[0];
+        zm_fence<T, SIG>();
+        // red, plane k - 1
+        zm_push(a0, zm_gs(rr[1] + zm_nb(buf(0, prv), c, c.x[prv], cx[1], cm[1], cp[1], e0[1], e0[2], e0[0]), iv.get(L, 0, k, 1)));
+        buf(1, cur)[c.lp] = a0[0];
+        zm_fence<T, SIG>();
+        // black, plane k - 2
+        zm_push(b0, zm_gs(rb[2] + zm_nb(buf(1, prv), c, c.x[prv], cx[2], cm[2], cp[2], a0[1], a0[2], a0[0]), iv.get(L, 1, k, 2)));
+        buf(2, cur)[c.lp] = b0[0];
+        zm_fence<T, SIG>();
+        // red, plane k - 3, and black, plane k - 4 (light: passed through)
+        const T a1n = zm_gs(rr[3] + zm_nb(buf(2, prv), c, c.x[prv], cx[3], cm[3], cp[3], b0[1], b0[2], b0[0]), iv.get(L, 0, k, 3));
+        zm_push(a1, two ? a1n : a0[2]);
+        buf(3, cur)[c.lp] = a1[0];
+        zm_fence<T, SIG>();
+        const T b1n = zm_gs(rb[4] + zm_nb(buf(3, prv), c, c.x[prv], cx[4], cm[4], cp[4], a1[1], a1[2], a1[0]), iv4);
+        const T fb = two ? b1n : b0[2];
+        // the finished pair, plane k - 4
+        const T fr = a1[1];
+        const int p = k - 4;
+        if (c.own && p >= c.z0 && p < c.z1) {
+            if (FINEST) {
+                const double lim = uniform_value((T)wt[3 * (p - c.k0) + 2]) != T(0) ? dmax : 1e300;
+                const double db = fmin(fmax((double)fb, -lim), lim), dr = fmin(fmax((double)fr, -lim), lim);
+                const bool odd = ((c.row + cur) & 1) == 0;         // the black cell is the pair's second
+                dpair v2;
+                v2.x = phk.x + (odd ? dr : db);
+                v2.y = phk.y + (odd ? db : dr);
+                *(dpair FX_AS(1) *)(phi_out + p * nxy) = v2;
+            } else {
+                L.e[p * plane + c.q0] = fr;
+                L.e[half + p * plane + c.q0] = fb;
+            }
+        }
+        // coarse plane K + 2 joins the ring for the next pair of planes
+        if (cur) {
+            cstore((k >> 1) + 2, zm_take(cnext));
+            cnext = cload((k >> 1) + 3);
+        }
+        __syncthreads();
+    };
+    zm_march(L, c.k0, k1, step);
+}
+
 // --------------------------------------------- coarse levels in one workgroup
 // Quotient q / d for 0 <= q < 2^20 and 1 <= d without an integer division: (q + 1/2) / d
 // lies at least 1/(2d) from the next integer, while the rounded product is off by at most
@@ -2873,6 +3424,18 @@ void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, 
     else launch_post_tb_f<T, 0>(I, w, level, nu, nz, nzc, st);
 }
 template <typename T>
+void launch_pre_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st) {
+    if (w.total <= 0) return;
+    hipLaunchKernelGGL(k_pre_zm<T>, grid_of(w.total), dim3(kZmThreads), zm_lds_bytes(zl, 0, sizeof(T)), st, I, w, level, nu, zl);
+}
+template <typename T>
+void launch_post_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st) {
+    if (w.total <= 0) return;
+    const size_t lds = zm_lds_bytes(zl, 1, sizeof(T));
+    if (level == 0) hipLaunchKernelGGL((k_post_zm<T, 1>), grid_of(w.total), dim3(kZmThreads), lds, st, I, w, level, nu, zl);
+    else hipLaunchKernelGGL((k_post_zm<T, 0>), grid_of(w.total), dim3(kZmThreads), lds, st, I, w, level, nu, zl);
+}
+template <typename T>
 void launch_coarse(const Inst<T> *I, InstState *S, int ninst, int lds_bytes, hipStream_t st) {
     hipLaunchKernelGGL(k_coarse<T>, dim3(ninst), dim3(kCoarseThreads), lds_bytes, st, I, S);
 }
@@ -2925,6 +3488,8 @@ void launch_fill(double *x, size_t n, double v, hipStream_t st) {
     template void launch_coarse<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                      \
     template void launch_pre_tb<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);                \
     template void launch_post_tb<T>(const Inst<T> *, const Work &, int, int, int, int, hipStream_t);          \
+    template void launch_pre_zm<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);                \
+    template void launch_post_zm<T>(const Inst<T> *, const Work &, int, int, int, hipStream_t);               \
     template void launch_head<T>(const Inst<T> *, InstState *, int, int, hipStream_t);                                    \
     template void launch_run_setup<T>(const Inst<T> *, int, int, int, double, int, hipStream_t);             \
     template void launch_set_vtop<T>(const Inst<T> *, int, double, hipStream_t);

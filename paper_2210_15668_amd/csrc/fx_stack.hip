@@ -350,7 +350,9 @@ struct Engine {
     ResWork w_res{};
     std::vector<Work> w_sm, w_rs, w_pr, w_prc;   // w_pr / w_prc: prolongation by fine or by coarse columns
     std::vector<Work> w_tb;             // blocked smoothing: a block per tile
-    std::vector<int> tb, tb_nz, tb_nzc; // level smoothed in blocks; the most planes on it and on the next
+    std::vector<int> tb, tb_nz, tb_nzc; // level smoothed in blocks (1: boxes of whole columns, 2: marching
+                                        // in z); the most planes on it and on the next
+    std::vector<int> zm_zl;             // planes per chunk of the march
     std::vector<int> prc_cz;            // coarse planes per thread of w_prc, per level
     std::vector<SmoothCfg> scfg;        // smoother launch shape per level
     std::vector<int> ncol;
@@ -438,16 +440,21 @@ int coarse_layout(const Plan &p, Inst<T> *a) {
 // forms it.
 bool fold_of(const Plan &p) { return p.lv[0].rb && p.lc > 0; }
 
-// Level l of p may be smoothed in blocks (k_pre_tb / k_post_tb): a red/black level with
-// launches of its own, halved in x and y into the next, no column twice in one box (extents of
-// at least a box edge), at most kTbMaxNz planes, and at most kTbCells cells: the blocks recompute
-// their rings, so they win while a level's launches are latency-bound (128 x 128 x 60: a
-// block per compute unit) and lose where the cells stream from HBM.
+// Level l of p may be smoothed in blocks: a red/black level with launches of its own, halved in x
+// and y into the next, with extents of at least a box edge.  Boxes of whole columns (k_pre_tb /
+// k_post_tb) take levels of up to kTbMaxNz planes and, over all instances, kTbCells cells; they
+// recompute a ring of 4 around 8 x 8 tiles, which costs least while the chip is not full.  Larger
+// levels march (k_pre_zm / k_post_zm).  A ramp of 128 x 128 x 48 (786 432 cells) takes 6.6 ms
+// with boxes and 7.6 ms with the march; 256 x 256 x 120 and 32 x 64 x 64 x 24 cells (7.9 and 3.1
+// million) take 231 and 141 us a cycle with the half-sweep launches and 159 and 64 with the march.
 constexpr size_t kTbCells = (size_t)1 << 20;
 bool tb_geom(const Plan &p, int l) {
     if (l >= p.lc) return false;
     const HostLevel &H = p.lv[l];
-    return H.rb && p.lv[l + 1].xy_from_finer == 1 && H.nx >= kTbW && H.ny >= kTbW && H.nz <= kTbMaxNz;
+    return H.rb && p.lv[l + 1].xy_from_finer == 1 && H.nx >= kTbW && H.ny >= kTbW;
+}
+int zm_tiles(const HostLevel &H, int zl) {
+    return ((H.nx + kZmT - 1) / kZmT) * ((H.ny + kZmT - 1) / kZmT) * ((H.nz + zl - 1) / zl);
 }
 // Levels whose black values between the two launches have an array of their own; the others
 // use the finer level's red half or, on the finest level, e's black half.
@@ -628,7 +635,7 @@ fx_status build_work(Engine *e) {
     e->w_res.cell0 = mk([&](const InstHost &h) { const Plan &p = h.plan; return tiles3(p.nx, p.ny, nzc(p)); });
     e->w_res.cell2 = mk([&](const InstHost &h) { const Plan &p = h.plan; return fold_of(p) ? 0 : tiles3(p.nx, p.ny, nzc(p)); });
     e->w_sm.clear(); e->w_rs.clear(); e->w_pr.clear(); e->w_prc.clear(); e->prc_cz.clear();
-    e->w_tb.clear(); e->tb.clear(); e->tb_nz.clear(); e->tb_nzc.clear();
+    e->w_tb.clear(); e->tb.clear(); e->tb_nz.clear(); e->tb_nzc.clear(); e->zm_zl.clear();
     const int cc_ok = env_int("FERROX_PROLONG_CC", 1) != 0;
     // the coarse-column prolongation: red/black fine level, x and y halved, z paired
     auto by_cc = [cc_ok](const Plan &p, int l) {
@@ -671,12 +678,29 @@ fx_status build_work(Engine *e) {
             nz = std::max(nz, h.plan.lv[l].nz);
             nzc = std::max(nzc, h.plan.lv[l + 1].nz);
         }
-        e->tb.push_back(ok && nz > 0 && cells <= kTbCells);
+        const bool boxes = cells <= kTbCells && nz <= kTbMaxNz;
+        e->tb.push_back(!ok || nz == 0 ? 0 : (boxes ? 1 : 2));
         e->tb_nz.push_back(nz);
         e->tb_nzc.push_back(nzc);
+        int zl = 0;
+        if (e->tb[l] == 2) {
+            // planes per chunk: the fewest steps of a compute unit over all its blocks (one block
+            // at a time).  32 at 256 x 256 x 120: 5.25 ms a pass against 6.6 with 8, 5.8 with 16
+            // and 6.2 with 60; 20 at 32 x 64 x 64 x 24
+            long long best = 0;
+            for (int z = 4; z <= std::min((nz + 1) / 2 * 2, kZmMaxZl) || zl == 0; z += 2) {
+                long long blocks = 0;
+                for (const InstHost &h : e->in)
+                    if (l < h.plan.lc) blocks += (long long)zm_tiles(h.plan.lv[l], z);
+                const long long cost = (blocks + 255) / 256 * (z + 2 * kZmH + 2);
+                if (zl == 0 || cost < best) { zl = z; best = cost; }
+            }
+        }
+        e->zm_zl.push_back(zl);
         e->w_tb.push_back(mk([&](const InstHost &h) {
             if (!e->tb[l] || l >= h.plan.lc) return 0;
-            return ((h.plan.lv[l].nx + kTbT - 1) / kTbT) * ((h.plan.lv[l].ny + kTbT - 1) / kTbT);
+            const HostLevel &H = h.plan.lv[l];
+            return e->tb[l] == 2 ? zm_tiles(H, zl) : ((H.nx + kTbT - 1) / kTbT) * ((H.ny + kTbT - 1) / kTbT);
         }));
     }
     if (bad) return fail(FX_EINVAL, "a launch would exceed 2^30 tiles");
@@ -933,7 +957,9 @@ void enq_vcycle(Engine *e) {
     const Inst<T> *I = idev<T>(e);
     for (int l = 0; l < e->max_lc; ++l) {
         if (blocked(e, l)) {                             // sweeps and restriction in blocks
-            launch_pre_tb(I, e->w_tb[l], l, l == 0 ? e->nu1 : e->nu1c, e->tb_nz[l], e->st);
+            const int nu = l == 0 ? e->nu1 : e->nu1c;
+            if (e->tb[l] == 2) launch_pre_zm(I, e->w_tb[l], l, nu, e->zm_zl[l], e->st);
+            else launch_pre_tb(I, e->w_tb[l], l, nu, e->tb_nz[l], e->st);
             continue;
         }
         const int nu1 = l == 0 ? e->nu1 : e->nu1c;
@@ -953,7 +979,9 @@ void enq_vcycle(Engine *e) {
     launch_coarse(I, e->st_dev, e->n, e->lds_max, e->st);
     for (int l = e->max_lc - 1; l >= 0; --l) {
         if (blocked(e, l)) {                             // prolongation and sweeps in blocks
-            launch_post_tb(I, e->w_tb[l], l, l == 0 ? e->nu2 : e->nu2c, e->tb_nz[l], e->tb_nzc[l], e->st);
+            const int nu = l == 0 ? e->nu2 : e->nu2c;
+            if (e->tb[l] == 2) launch_post_zm(I, e->w_tb[l], l, nu, e->zm_zl[l], e->st);
+            else launch_post_tb(I, e->w_tb[l], l, nu, e->tb_nz[l], e->tb_nzc[l], e->st);
             continue;
         }
         const int nu2 = l == 0 ? e->nu2 : e->nu2c;
