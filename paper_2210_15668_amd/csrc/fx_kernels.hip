@@ -3052,7 +3052,20 @@ __device__ __forceinline__ void bottom_cg_block(const Lv<T, 3> &B, T FX_AS(3) *r
     __syncthreads();
 }
 
-// The bottom solve by the whole workgroup (n > 64) or by its first wave.
+// The bottom solve by the whole workgroup (n > 64) or by its first wave.  The coarsest level
+// holds e, r and two vectors in kCoarseLdsBytes: at most 2048 cells in FP64 and 4096 in FP32,
+// which every instantiation's cells per thread must cover.
+static_assert(kCoarseLdsBytes / (4 * sizeof(double)) <= 2 * kCoarseThreads &&
+                  kCoarseLdsBytes / (4 * sizeof(float)) <= 4 * kCoarseThreads,
+              "cells per thread of the bottom solve");
+template <typename T>
+__device__ __forceinline__ void bottom_block(const Lv<T, 3> &B, T FX_AS(3) *rs, double FX_AS(3) *red, int iters,
+                                             double tol2) {
+    const int n = B.nx * B.ny * B.nz;
+    if (n <= kCoarseThreads) bottom_cg_block<T, 1>(B, rs, red, iters, tol2);
+    else if (n <= 2 * kCoarseThreads) bottom_cg_block<T, 2>(B, rs, red, iters, tol2);
+    else if constexpr (sizeof(T) == 4) bottom_cg_block<T, 4>(B, rs, red, iters, tol2);
+}
 template <typename T>
 __device__ __forceinline__ void bottom_wave(const Lv<T, 3> &B, int iters, double tol2) {
     if (B.nx * B.ny * B.nz <= 8) bottom_direct(B);
@@ -3203,8 +3216,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(const Inst<T> *I, Ins
         const Lv<T, 3> B = lvl(nl - 1);
         T FX_AS(3) *rs = (T FX_AS(3) *)(lds + A.off_p);
         double FX_AS(3) *red = (double FX_AS(3) *)(lds + A.off_q);       // more than 64 cells: room for 32
-        if (B.nx * B.ny * B.nz <= kCoarseThreads) bottom_cg_block<T, 1>(B, rs, red, A.bottom_iters, A.bottom_tol2);
-        else bottom_cg_block<T, 2>(B, rs, red, A.bottom_iters, A.bottom_tol2);
+        bottom_block<T>(B, rs, red, A.bottom_iters, A.bottom_tol2);
     } else {
         if (threadIdx.x < 64) {
             for (int q = qw; q < nl - 1; ++q) co_down<1>(lvl(q), lvl(q + 1), xlds(q), nu1);
