@@ -444,7 +444,7 @@ bool fold_of(const Plan &p) { return p.lv[0].rb && p.lc > 0; }
 // and y into the next, with extents of at least a box edge.  Boxes of whole columns (k_pre_tb /
 // k_post_tb) take levels of up to kTbMaxNz planes and, over all instances, kTbCells cells; they
 // recompute a ring of 4 around 8 x 8 tiles, which costs least while the chip is not full.  Larger
-// levels march (k_pre_zm / k_post_zm).  A ramp of 128 x 128 x 48 (786 432 cells) takes 6.6 ms
+// levels march (k_pre_zm / k_post_zm) where march_pays.  A ramp of 128 x 128 x 48 (786 432 cells) takes 6.6 ms
 // with boxes and 7.6 ms with the march; 256 x 256 x 120 and 32 x 64 x 64 x 24 cells (7.9 and 3.1
 // million) take 231 and 141 us a cycle with the half-sweep launches and 159 and 64 with the march.
 constexpr size_t kTbCells = (size_t)1 << 20;
@@ -603,6 +603,46 @@ void put_table(Engine *e, const void *dst, const void *src, size_t bytes) {
     memcpy(e->tab_host.data() + ((const char *)dst - e->tab_dev), src, bytes);
 }
 
+// Planes per chunk of the march on level l (of at most nz planes), and the rounds of blocks it takes
+// (a block at a time on each of 256 compute units): the fewest steps of a compute unit over all its
+// blocks.  32 planes at 256 x 256 x 120: 5.25 ms a pass against 6.6 with 8, 5.8 with 16 and 6.2
+// with 60; 20 at 32 x 64 x 64 x 24.
+int zm_chunk(const Engine *e, int l, int nz, long long *rounds) {
+    int zl = 0;
+    long long best = 0;
+    for (int z = 4; z <= std::min((nz + 1) / 2 * 2, kZmMaxZl) || zl == 0; z += 2) {
+        long long blocks = 0;
+        for (const InstHost &h : e->in)
+            if (l < h.plan.lc) blocks += (long long)zm_tiles(h.plan.lv[l], z);
+        const long long r = (blocks + 255) / 256, cost = r * (z + 2 * kZmH + 2);
+        if (zl == 0 || cost < best) { zl = z; best = cost; *rounds = r; }
+    }
+    return zl;
+}
+
+// The march against the level's half-sweep launches, in microseconds a cycle.  A march takes its
+// steps, whatever part of its tiles lies in the grid, and in a light cycle as long as in a full
+// one; the launches take about 30 us and their traffic, over the cells of whole tiles, and a light
+// cycle costs them three quarters of a full one (stacks with a semiconductor take one in every two
+// or three cycles).  The constants are fits to both sides' times on 100 stacks and batches of
+// 16 x 16 to 1024 x 1024 columns and 12 to 500 planes; of the two the chosen one was never
+// more than 6% the slower.  Whole time steps in us, march / launches: FP64 256 x 256 x 120 (64
+// semiconductor planes) 587 / 672, mixed 490 / 505; mixed 384 x 384 x 160 (60) 1845 / 1733;
+// FP64 80 x 80 x 150 (70) both levels 493 / 416; batch of 256 x 34 x 34 x 24 1196 / 1699.
+bool march_pays(const Engine *e, int l, int zl, int nz, long long rounds, size_t cells) {
+    const bool fp64 = e->prec == FX_PREC_FP64;
+    bool sig = false;
+    for (const InstHost &h : e->in)
+        if (l < h.plan.lc) sig |= h.plan.lv[l].sig_hi > h.plan.lv[l].sig_lo;
+    const double step = fp64 ? (sig ? 1.8 : 1.2) : (sig ? 1.55 : 0.85);
+    const int steps = zl + (zl < nz ? 2 : 1) * kZmH + 1;
+    const double march = 2.0 * rounds * (5.0 + steps * step);
+    const double tiled = 512.0 * e->scfg[l].zt * e->w_sm[l].total;      // both colours' cells
+    // FP32 levels of more than 24 million cells do not fit the last-level cache
+    const double per_cell = fp64 ? 26e-6 : (cells > 24000000 ? 23e-6 : 17e-6);
+    return march < 1.03 * (30.0 + per_cell * tiled) * (sig ? 0.87 : 1.0);
+}
+
 // Prefix tables of per-instance tile counts, one per launch kind.
 fx_status build_work(Engine *e) {
     const int n = e->n;
@@ -667,8 +707,10 @@ fx_status build_work(Engine *e) {
             const HostLevel &C = h.plan.lv[l + 1];
             return tiles3(C.nx, C.ny, (C.nz + cz - 1) / cz);
         }));
-        // blocked smoothing where every instance that has this level qualifies
-        bool ok = e->fuse && env_int("FERROX_TB", 1) != 0 && (l == 0 ? e->nu1 <= 2 && e->nu2 <= 2 : e->nu1c <= 2 && e->nu2c <= 2);
+        // blocked smoothing where every instance that has this level qualifies (FERROX_TB: 0
+        // nowhere, 1 wherever it can run, else also only where it pays)
+        const int tb = env_int("FERROX_TB", -1);
+        bool ok = e->fuse && tb != 0 && (l == 0 ? e->nu1 <= 2 && e->nu2 <= 2 : e->nu1c <= 2 && e->nu2c <= 2);
         int nz = 0, nzc = 0;
         size_t cells = 0;
         for (const InstHost &h : e->in) {
@@ -679,23 +721,15 @@ fx_status build_work(Engine *e) {
             nzc = std::max(nzc, h.plan.lv[l + 1].nz);
         }
         const bool boxes = cells <= kTbCells && nz <= kTbMaxNz;
-        e->tb.push_back(!ok || nz == 0 ? 0 : (boxes ? 1 : 2));
+        int mode = !ok || nz == 0 ? 0 : (boxes ? 1 : 2), zl = 0;
+        if (mode == 2) {
+            long long rounds = 0;
+            zl = zm_chunk(e, l, nz, &rounds);
+            if (tb != 1 && !march_pays(e, l, zl, nz, rounds, cells)) mode = 0;
+        }
+        e->tb.push_back(mode);
         e->tb_nz.push_back(nz);
         e->tb_nzc.push_back(nzc);
-        int zl = 0;
-        if (e->tb[l] == 2) {
-            // planes per chunk: the fewest steps of a compute unit over all its blocks (one block
-            // at a time).  32 at 256 x 256 x 120: 5.25 ms a pass against 6.6 with 8, 5.8 with 16
-            // and 6.2 with 60; 20 at 32 x 64 x 64 x 24
-            long long best = 0;
-            for (int z = 4; z <= std::min((nz + 1) / 2 * 2, kZmMaxZl) || zl == 0; z += 2) {
-                long long blocks = 0;
-                for (const InstHost &h : e->in)
-                    if (l < h.plan.lc) blocks += (long long)zm_tiles(h.plan.lv[l], z);
-                const long long cost = (blocks + 255) / 256 * (z + 2 * kZmH + 2);
-                if (zl == 0 || cost < best) { zl = z; best = cost; }
-            }
-        }
         e->zm_zl.push_back(zl);
         e->w_tb.push_back(mk([&](const InstHost &h) {
             if (!e->tb[l] || l >= h.plan.lc) return 0;
