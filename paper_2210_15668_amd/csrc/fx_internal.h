@@ -82,7 +82,8 @@ static_assert(tb_lds_bytes(kTbMaxNz, kTbMaxNz / 2, sizeof(double)) <= 160 * 1024
 constexpr int kZmT = 32;                   // tile edge (cells)
 constexpr int kZmH = 4;                    // ring and halo planes
 constexpr int kZmMaxZl = 96;               // planes per chunk
-// planes in a march's tables: the chunk, its halo, and up to 3 steps of the last group of four
+// planes in a march's tables: the chunk, its halo, and the steps after it (the restriction's last
+// odd rows, and one that makes their number even)
 __host__ __device__ constexpr int kZmTab(int zl) { return zl + 2 * kZmH + 4; }
 __host__ __device__ constexpr size_t zm_lds_bytes(int zl, int post, size_t w) {
     const size_t cells = (size_t)(kZmT + 2 * kZmH) / 2 * (kZmT + 2 * kZmH), plane = cells + 48, cw = (kZmT + 2 * kZmH) / 2 + 2;
@@ -203,7 +204,7 @@ struct Inst {
     int off_e[kMaxLevels], off_r[kMaxLevels], off_s[kMaxLevels], off_t[kMaxLevels];
     int off_x[kMaxLevels];             // transfer tables between coarse-kernel levels q and q+1
     // conjugate-gradient bottom solve: shared vector, reduction scratch (LDS offsets)
-    int off_p, off_q, off_red;
+    int off_p, off_red;
     int bottom_iters;
     int wave_lev;                      // first coarse-kernel level run by one wave (levels from lc; nlev - lc: none)
     double bottom_tol2;
@@ -274,7 +275,7 @@ template <typename T> void launch_coarse(const Inst<T> *I, InstState *S, int nin
 // tile; nz, nzc: the most planes of an instance on this level and the next
 template <typename T> void launch_pre_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, hipStream_t st);
 template <typename T> void launch_post_tb(const Inst<T> *I, const Work &w, int level, int nu, int nz, int nzc, hipStream_t st);
-// the same on a level of any size, in z-chunks of zl planes (a multiple of 4)
+// the same on a level of any size, in z-chunks of zl planes (an even number)
 template <typename T> void launch_pre_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st);
 template <typename T> void launch_post_zm(const Inst<T> *I, const Work &w, int level, int nu, int zl, hipStream_t st);
 template <typename T> void launch_head(const Inst<T> *I, InstState *S, int ninst, int advance, hipStream_t st);

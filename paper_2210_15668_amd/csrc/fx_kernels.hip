@@ -2750,17 +2750,20 @@ __device__ __forceinline__ void co_smooth_nat(const Lv<T, 3> &L, int nu, int zer
 }
 
 // Pre-smoothing and restriction, and prolongation and post-smoothing, of one level.  A red/black
-// level here holds e and r in kCoarseLdsBytes, so at most 4096 cells in FP64 and 8192 in FP32; a
-// plainly stored one has at most kCoarseNatCells where it takes more than that, and so 8192.
-static_assert(kCoarseLdsBytes / (2 * sizeof(float)) <= 8 * kCoarseThreads && kCoarseNatCells <= 4 * kCoarseThreads,
+// level here holds e and r in kCoarseLdsBytes, so at most 4096 cells in FP64 and 8192 in FP32.  A
+// plainly stored one is halved in z alone: with the levels below it (half of it, a quarter, ..., the
+// bottom's four vectors) it takes four vectors of its cells, so at most 4096 where all fit
+// kCoarseLdsBytes, and kCoarseNatCells where they take more.
+static_assert(kCoarseLdsBytes / (2 * sizeof(double)) <= 4 * kCoarseThreads &&
+                  kCoarseLdsBytes / (2 * sizeof(float)) <= 8 * kCoarseThreads &&
+                  kCoarseLdsBytes / (4 * sizeof(float)) <= 4 * kCoarseThreads && kCoarseNatCells <= 4 * kCoarseThreads,
               "cells per thread");
 template <typename T>
 __device__ __forceinline__ void co_nat(const Lv<T, 3> &L, int nu, int zero_init) {
     const int n = L.nx * L.ny * L.nz;
     if (n <= kCoarseThreads) co_smooth_nat<T, 1, 0>(L, nu, zero_init);
     else if (n <= 2 * kCoarseThreads) co_smooth_nat<T, 2, 0>(L, nu, zero_init);
-    else if (n <= 4 * kCoarseThreads) co_smooth_nat<T, 4, 0>(L, nu, zero_init);
-    else if constexpr (sizeof(T) == 4) co_smooth_nat<T, 8, 0>(L, nu, zero_init);
+    else co_smooth_nat<T, 4, 0>(L, nu, zero_init);
 }
 template <int W, typename T, typename X_>
 __device__ __forceinline__ void co_down(const Lv<T, 3> &L, const Lv<T, 3> &C, const X_ &X, int nu) {
@@ -3215,7 +3218,7 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(const Inst<T> *I, Ins
     if (qw >= nl) {
         const Lv<T, 3> B = lvl(nl - 1);
         T FX_AS(3) *rs = (T FX_AS(3) *)(lds + A.off_p);
-        double FX_AS(3) *red = (double FX_AS(3) *)(lds + A.off_q);       // more than 64 cells: room for 32
+        double FX_AS(3) *red = (double FX_AS(3) *)(lds + A.off_red);     // more than 64 cells: room for 32
         bottom_block<T>(B, rs, red, A.bottom_iters, A.bottom_tol2);
     } else {
         if (threadIdx.x < 64) {

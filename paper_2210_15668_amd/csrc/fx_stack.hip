@@ -428,10 +428,11 @@ int coarse_layout(const Plan &p, Inst<T> *a) {
         const int ox = take(3 * nc * sizeof(int) + 3 * nf * sizeof(int) + 2 * nf * sizeof(T) + 16);
         if (a) a->off_x[q] = ox;
     }
+    // bottom solve: the shared vector and the room of a second one, which the sums use; with e and r
+    // these four bound the coarsest level's cells
     const HostLevel &B = p.lv.back();
-    const int op = take(B.ncell() * sizeof(T)), oq = take(B.ncell() * sizeof(T));
-    const int ored = take(16 * sizeof(double));
-    if (a) { a->off_p = op; a->off_q = oq; a->off_red = ored; }
+    const int op = take(B.ncell() * sizeof(T)), ored = take(B.ncell() * sizeof(T) + 16 * sizeof(double));
+    if (a) { a->off_p = op; a->off_red = ored; }
     return off;
 }
 
@@ -457,7 +458,9 @@ int zm_tiles(const HostLevel &H, int zl) {
     return ((H.nx + kZmT - 1) / kZmT) * ((H.ny + kZmT - 1) / kZmT) * ((H.nz + zl - 1) / zl);
 }
 // Levels whose black values between the two launches have an array of their own; the others
-// use the finer level's red half or, on the finest level, e's black half.
+// use the finer level's red half or, on the finest level, e's black half (make_inst).  Any level
+// below the finest could do without: these keep theirs so that the workspace sizes, which
+// callers allocate and the static workspace is compared with, stay what they were.
 bool tb_own_array(const Plan &p, int l, size_t w) {
     if (l < 1 || !tb_geom(p, l)) return false;
     const HostLevel &H = p.lv[l];
