@@ -10,8 +10,9 @@ A step is the forward-Euler TDGL update plus the nonlinear Poisson solve to
 the warm-up steps are outside the timed region; fields are resident in HBM.
 
 Prints one JSON line: FP64 steps/s (headline), the mixed-precision variant, the
-roofline of the dominant kernel (the finest-level Gauss-Seidel half-sweep, timed
-by its own dispatch events inside the timed region) and the CPU oracle's rate on
+roofline of the finest-level Gauss-Seidel half-sweep (timed by its own dispatch events in
+a run of its own: the timed region smooths that level in blocks, two launches a cycle,
+which the probe's separate half-sweeps replace) and the CPU oracle's rate on
 a bounded sample of the same stack.  Beside them: the batch of 64 uneven instances, the
 learned warm start, and the same stack with the predictor-corrector time scheme and with
 Fermi-Dirac carriers, plus a recorded Q-V sweep of the 3D MFIM of the Results.
@@ -68,36 +69,38 @@ def run_gpu(prec_name, steps, warmup, tune=True, tune_cache=None):
     if warmup:
         s.run_steps(warmup, W.DT)
     torch.cuda.synchronize()
-    # every 7th finest-level smoother launch of the timed region is timed by its own
-    # dispatch events (timing every launch would slow the region by a few per cent);
-    # 7 is prime to the 8 such launches of a V-cycle, so all variants are sampled
-    s.probe(ferrox.PROBE_SMOOTH_FINE, max_launches=min(4096, max(64, steps * 2)), stride=7)
     t0 = time.perf_counter()
     info = s.run_steps(steps, W.DT)
     torch.cuda.synchronize()
     t1 = time.perf_counter()
+    out = {"phi": s.phi.detach().cpu().numpy()}
+    # the finest level's half-sweeps as launches of their own, outside the timed region: every
+    # 7th is timed by its own dispatch events (7 is prime to the 8 such launches of a V-cycle,
+    # so all variants are sampled)
+    s.probe(ferrox.PROBE_SMOOTH_FINE, max_launches=min(4096, max(64, steps * 2)), stride=7)
+    s.run_steps(min(steps, 100), W.DT)
     ms, launches, nbytes = s.probe_read()
     s.probe(ferrox.PROBE_OFF)
     elapsed = t1 - t0
-    out = {
+    out |= {
         "steps_per_s": steps / elapsed,
         "ms_per_step": 1e3 * elapsed / steps,
         "vcycles_per_step": info.total_cycles / max(1, steps),
         "last_rel_residual": info.last_res_rel,
         "probe_ms": ms, "probe_launches": launches, "probe_bytes": nbytes, "autotune": tuned,
     }
-    out["phi"] = s.phi.detach().cpu().numpy()
     s.close()
     return out
 
 
 def model_bytes_per_step(spec, vcycles, prec_name):
     """The one-touch byte model of a time step: the TDGL update reads P and phi and writes P
-    (24 B per ferroelectric cell); each V(2,2) cycle moves about 149 B (FP64) or 114 B (FP32
-    multigrid inside the FP64 defect correction) per device cell over all levels, residual
-    and update included; the residual of the starting iterate reads phi and writes r (24 B,
+    (24 B per ferroelectric cell); each V(2,2) cycle moves about 85 B (FP64) or 58 B (FP32
+    multigrid inside the FP64 defect correction) per device cell over all levels: two launches
+    a level that each read r and sigma once and pass the black values on, phi read and written,
+    and the residual; the residual of the starting iterate reads phi and writes r (24 B,
     mixed 20 B per device cell)."""
-    per_cycle, per_res = (149.0, 24.0) if prec_name == "fp64" else (114.0, 20.0)
+    per_cycle, per_res = (85.0, 24.0) if prec_name == "fp64" else (58.0, 20.0)
     return 24.0 * spec.n_fe() + (vcycles * per_cycle + per_res) * spec.n_active()
 
 
@@ -395,7 +398,7 @@ def main():
     traffic = measured_traffic("fp64")
     roofline = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                "kernel": "k_smooth / k_smooth_w8 <double, ...> (finest-level red/black Gauss-Seidel half-sweep, FP64, all variants; launches a light cycle leaves empty are not counted)",
+                "kernel": "k_smooth / k_smooth_w8 <double, ...> (finest-level red/black Gauss-Seidel half-sweep, FP64, all variants; launches a light cycle leaves empty are not counted), launched one by one for the probe; the timed region runs this level in k_pre_zm / k_post_zm",
                 "avg_launch_us": avg_us, "algorithmic_bytes_per_launch": per_launch,
                 "launches_timed": r64["probe_launches"]}
     batch = None
