@@ -272,8 +272,9 @@ fx_status set_field(fx_stack *s, int which, const double *h_in);
  * Launches in which every solve had already stopped do no work and are not
  * counted.  stack_probe resets the counters (and synchronises the stream);
  * stack_probe_read synchronises and returns the summed duration in ms, the
- * number of counted launches and their bytes.  Runs use kernel-by-kernel
- * launches while the probe is on. */
+ * number of counted launches and their bytes.  While the probe is on, runs use
+ * kernel-by-kernel launches, and a finest level that is otherwise smoothed in
+ * blocks takes its half-sweep launches (the same bits, more time). */
 enum { FX_PROBE_OFF = 0, FX_PROBE_SMOOTH_FINE = 1 };
 fx_status stack_probe(fx_stack *s, int kernel, int max_launches, int stride);
 fx_status stack_probe_read(fx_stack *s, double *total_ms, int *launches, double *bytes);
@@ -289,19 +290,21 @@ fx_status stack_probe_read(fx_stack *s, double *total_ms, int *launches, double 
 enum { FX_LAUNCH_STREAM = 0, FX_LAUNCH_GRAPH = 1 };
 fx_status stack_set_launch(fx_stack *s, int mode);
 
-/* Autotuner.  For every multigrid level with its own smoother launches,
- * times the candidate launch shapes of the Gauss-Seidel half-sweep on the
- * stack's own level arrays -- tiles of 32x8, 64x4 or 128x2 threads, 1, 2, 4
- * or 8 planes per thread (z-march length), and the compiler's register
- * budget or one that keeps 8 waves per SIMD resident -- and keeps the
- * fastest.  Only the division of the work changes, so results are bitwise
+/* Autotuner.  For every multigrid level above the coarse kernel, times the
+ * candidate launch shapes of the Gauss-Seidel half-sweep on the stack's own
+ * level arrays -- tiles of 32x8, 64x4 or 128x2 threads, 1, 2, 4 or 8 planes
+ * per thread (z-march length), and the compiler's register budget or one
+ * that keeps 8 waves per SIMD resident -- and keeps the fastest.  Only the division of the work changes, so results are bitwise
  * identical with any choice.  cache_path (NULL: none) names a text file of
  * earlier choices keyed by GPU architecture, precision and the shapes of the
  * level's instances: a level found there is not timed again unless
  * FX_TUNE_FORCE is set; new choices are appended.  Synchronises the stream;
- * call between runs (not while a probe is on).  info may be NULL. */
+ * call between runs (not while a probe is on).  A level that is smoothed in
+ * blocks (FX_LEVEL_BLOCKED) is timed too, but uses its shape only where its
+ * half-sweeps are launched: on the finest level while a probe is on.  info
+ * may be NULL. */
 typedef struct {
-    int levels;                  /* levels with their own smoother launches                  */
+    int levels;                  /* levels above the coarse kernel                           */
     int from_cache;              /* of those, shapes taken from the cache file               */
     int configs_timed;           /* candidate shapes timed                                   */
     int cache_written;           /* 1 if new lines were appended to the cache file           */
