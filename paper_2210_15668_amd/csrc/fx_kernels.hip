@@ -1947,11 +1947,12 @@ __global__ __launch_bounds__(kTbThreads) void k_post_tb(const Inst<T> *I, Work w
 //
 // What bounds it: on 256 x 256 x 120 cells the half-sweep launches and transfers of a cycle read
 // and write 1.2 GB (231 us); here r, sigma, phi and the black values are read once per launch
-// (0.57 GB with the rings, by counters), and the latency of a step's chain of LDS reads, FP64
-// operations and barrier over 1.56 x (zl + 8) / zl cell updates takes over: 77 + 82 us
+// (0.59 GB with the rings, FP32 0.37, by counters), and the latency of a step's chain of LDS reads,
+// FP64 operations and barrier over 1.56 x (zl + 8) / zl cell updates takes over: 77 + 82 us
 // (FP32 65 + 60, launches 138; 32 instances of 64 x 64 x 24: 29 + 35, launches 141).  Tiles of
 // 32 x 16 with two blocks per compute unit measured 82 + 87, 68 + 64 and 27 + 34; an order of the
-// tiles that shares more of the rings in L2 fetched 15% less in the same time.
+// tiles that shares more of the rings in L2 fetched 15% less in the same time.  The form without
+// spaced waits and scalar extents took 71 + 78, FP32 57 + 56, and 29 + 37 on the 32 instances.
 constexpr int kZmThreads = 832;               // 800 pairs of the box, whole waves
 constexpr int kZmP = (kZmT + 2 * kZmH) / 2;   // pairs per box row
 constexpr int kZmN = kZmP * (kZmT + 2 * kZmH);
