@@ -196,7 +196,10 @@ __device__ __forceinline__ void gs_cell(const V &L, int i, int j, int k, int zer
 // odd periodic extent the parity colouring makes the wrap neighbours equal
 // coloured, so the last column / row (for odd nx / ny) get colours 2 and 3:
 // no two cells of one colour are then neighbours, and a sweep is the four
-// colours in turn.
+// colours in turn.  With both extents odd one corner is left: of a plane's cells
+// (nx-1, 0), (0, ny-1) and (nx-1, ny-1), all of one colour, the last is a neighbour
+// of the others.  A launched sweep then reads there either the new or the old value,
+// so two runs may differ in the last bits; the coarse kernel orders the two with a barrier.
 template <typename V>
 __device__ __forceinline__ int nat_color(const V &L, int i, int j, int k) {
     const int par = (i + j + k) & 1;
